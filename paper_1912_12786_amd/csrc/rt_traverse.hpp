@@ -205,13 +205,29 @@ __device__ __forceinline__ bool triangle(const ray_state &r, float4 a, float4 b,
 }
 
 // -------------------------------------------------------------------------
-// traversal stack: a ring of kSlots entries per lane in LDS holds the top of
-// the stack; when a push would overflow it, the oldest entry moves to a
-// per-lane column of global memory, and pops below the ring read it back.
-// Every entry survives, so the per-ray visit order never depends on kSlots.
-// Entries [0, base) live in global memory, [base, sp) in the ring at slot
-// i & (kSlots - 1); at most kSlots - 1 live in the ring, so the slot at sp is
-// always free and a push can write it before knowing whether it is kept.
+// traversal stack: the top entry in registers, the kSlots below it in a ring
+// per lane in LDS; when a push would overflow the ring, its oldest entry moves
+// to a per-lane column of global memory, and once the ring is empty pops read
+// that column back.  Every entry survives, so the per-ray visit order never
+// depends on kSlots.
+//
+// The bottom of the stack is a sentinel, (kNoRef, -inf): no bound culls it, so
+// popping it ends the ray without a test for an empty stack, and a nested
+// traversal ends at a sentinel of its own.  With the top in registers a pop
+// needs no LDS read before the next node's fetch -- the entry below is loaded
+// while that fetch is in flight -- and the ring position is kept as the byte
+// offset of the next free slot, lane included, so a push or a pop is an add
+// and a mask.  A stack of at most d entries and s sentinels fits a column of
+// d - (kSlots - 1) when s <= 2: 1 + kSlots + d - (kSlots - 1) = d + 2.
+//
+// The traversal step is bound by instruction issue (vector ALU and texture
+// addresser about equally) on large launches and by the latency of its chain
+// on small ones, so what surrounds the two slab tests counts: against a ring
+// popped by a loop with a floor, an `active` flag per lane and per-lane spill
+// addresses, this stack and the loop around it took the 1080p alpha closest
+// hit from 578 to 496 us, 4,096 rays in 1,024 triangles from 46.7 to 39.6 us,
+// 3.7 M rays in 1 M triangles from 1,019 to 935 us and 32 scenes in one
+// launch from 889 to 791 us, every result the same.
 // -------------------------------------------------------------------------
 // A pointer into global memory (address space 1).  Typing the spill column
 // this way keeps the compiler from merging its accesses with the LDS ring's
@@ -219,64 +235,99 @@ __device__ __forceinline__ bool triangle(const ray_state &r, float4 a, float4 b,
 template <class T>
 using global_ptr = __attribute__((address_space(1))) T *;
 
+// The reference of a finished lane and of a sentinel; no node or leaf has it
+// (a leaf of 7 triangles at index 2^29 - 1 would end past the largest
+// triangle count).
+constexpr uint32_t kNoRef = 0xFFFFFFFFu;
+
+// A stack entry: the reference in the low word, the bits of tn in the high one
+// (one 64-bit value, so that an LDS read lands in the entry's own registers).
+__device__ __forceinline__ uint64_t stack_entry(uint32_t ref, float tn)
+{
+    return uint64_t(ref) | (uint64_t(__float_as_uint(tn)) << 32);
+}
+constexpr uint64_t kSentinel = 0xFF80000000000000ull | kNoRef;  // (kNoRef, -inf)
+
 template <int kSlots, int kBlock>
 struct ring_stack {
     static_assert((kSlots & (kSlots - 1)) == 0 && kSlots >= 2, "kSlots: power of two >= 2");
-    static constexpr uint32_t kMask = kSlots - 1;
-    uint2 (*ring)[kBlock];  // [kSlots][kBlock] in LDS
-    global_ptr<uint64_t> spill;  // this lane's column: entry i at spill[i * stride]
-    uint32_t tid, stride;
-    uint32_t sp = 0, base = 0;
-    uint32_t floor = 0;  // pops stop here (a nested traversal owns [floor, sp))
+    static_assert((kBlock & (kBlock - 1)) == 0, "kBlock: power of two");
+    static constexpr uint32_t kStride = uint32_t(kBlock) * sizeof(uint64_t);
+    static constexpr uint32_t kBytes = uint32_t(kSlots) * kStride;
+    unsigned char *ring;         // [kSlots][kBlock] entries in LDS
+    global_ptr<uint64_t> spill;  // columns of all lanes: entry i of lane g at [i * lanes + g]
+    uint32_t at;                 // byte offset of the lane's next free slot
+    int held = 0;                // entries in the ring: the held slots before `at`
+    uint32_t spilled = 0;        // entries in the column, all older than the ring's
+    uint64_t top = kSentinel;
 
+    __device__ __forceinline__ ring_stack(uint64_t *lds, uint64_t *columns)
+        : ring(reinterpret_cast<unsigned char *>(lds)), spill((global_ptr<uint64_t>)columns),
+          at(threadIdx.x * uint32_t(sizeof(uint64_t)))
+    {
+    }
+
+    __device__ __forceinline__ uint64_t &slot(uint32_t offset)
+    {
+        return *reinterpret_cast<uint64_t *>(ring + offset);
+    }
+
+    // An empty stack (the ring may start at any slot).
     __device__ __forceinline__ void reset()
     {
-        sp = 0;
-        base = 0;
-        floor = 0;
+        held = 0;
+        spilled = 0;
+        top = kSentinel;
     }
 
-    // Writes e into the free slot; keeps it iff `keep`.
-    __device__ __forceinline__ void push_if(bool keep, uint2 e)
+    __device__ __forceinline__ void push(uint64_t e)
     {
-        ring[sp & kMask][tid] = e;
-        if (keep) {
-            ++sp;
-            if (sp - base == kSlots) {  // ring full: evict the oldest entry
-                spill_store(base, ring[base & kMask][tid]);
-                ++base;
-            }
+        if (__builtin_expect(held == kSlots, 0)) spill[column(spilled++)] = slot(at);  // the oldest
+        slot(at) = top;
+        at = (at + kStride) & (kBytes - 1);
+        held = min(held + 1, kSlots);
+        top = e;
+    }
+
+    // Drops the top entry: the one below it becomes the top, below the bottom
+    // sentinel another sentinel.
+    __device__ __forceinline__ void drop()
+    {
+        const uint32_t below = (at - kStride) & (kBytes - 1);
+        // read whether or not the ring holds an entry (the slot is the lane's
+        // own either way): the usual path then neither branches nor waits
+        top = slot(below);
+        if (__builtin_expect(held != 0, 1)) {
+            at = below;
+            --held;
+        } else {
+            // keeps the read above the branch
+            asm volatile("" : "+v"(top));
+            top = kSentinel;
+            if (spilled != 0) top = spill[column(--spilled)];
         }
     }
 
-    // Pops until an entry with tn <= tmax appears; false when empty.
-    __device__ __forceinline__ bool pop(float tmax, uint32_t &ref)
+    // The reference of the topmost entry with tn <= tmax, entries above it
+    // dropped; kNoRef at a sentinel.  kCulls false: tmax has not moved since
+    // any entry was pushed, so the first one qualifies (a box is pushed only
+    // if tn <= tf <= tmax).
+    template <bool kCulls>
+    __device__ __forceinline__ uint32_t pop(float tmax)
     {
-        while (sp > floor) {
-            --sp;
-            uint2 e;
-            if (sp >= base) {
-                e = ring[sp & kMask][tid];
-            } else {
-                e = spill_load(sp);
-                base = sp;
-            }
-            if (!(__uint_as_float(e.y) > tmax)) {
-                ref = e.x;
-                return true;
-            }
-        }
-        return false;
+        if constexpr (kCulls)
+            while (__builtin_expect(__uint_as_float(uint32_t(top >> 32)) > tmax, 0)) drop();
+        const uint32_t ref = uint32_t(top);
+        drop();
+        return ref;
     }
 
-    __device__ __forceinline__ void spill_store(uint32_t i, uint2 e)
+    // Index of entry i of this lane's column; the lane's number comes from
+    // `at`, so the rarely needed address takes no registers between uses.
+    __device__ __forceinline__ size_t column(uint32_t i) const
     {
-        spill[size_t(i) * stride] = uint64_t(e.x) | (uint64_t(e.y) << 32);
-    }
-    __device__ __forceinline__ uint2 spill_load(uint32_t i) const
-    {
-        const uint64_t v = spill[size_t(i) * stride];
-        return make_uint2(uint32_t(v), uint32_t(v >> 32));
+        const uint32_t tid = (at & (kStride - 1)) / uint32_t(sizeof(uint64_t));
+        return size_t(i) * (gridDim.x * uint32_t(kBlock)) + (blockIdx.x * uint32_t(kBlock) + tid);
     }
 };
 
@@ -376,9 +427,9 @@ __device__ __forceinline__ void order2(uint64_t &a, uint64_t &b)
 // child slot, visit the nearest hit child (ties -> the lower slot) and push
 // the other hit ones from the farthest to the second nearest; with none hit,
 // pop.  The four keys are ordered by a five-comparator sorting network.
-template <class Isect, class Stack>
-__device__ __forceinline__ bool inner_step_wide(const scene_view &sc, const ray_state &r,
-                                                Isect &isect, Stack &st, uint32_t &cur)
+template <bool kCulls, class Isect, class Stack>
+__device__ __forceinline__ uint32_t inner_step_wide(const scene_view &sc, const ray_state &r,
+                                                    Isect &isect, Stack &st, uint32_t cur)
 {
     const float4 *nd = sc.nodes + 8 * size_t(cur);
     const uint4 rf = *reinterpret_cast<const uint4 *>(nd + 6);
@@ -413,24 +464,23 @@ __device__ __forceinline__ bool inner_step_wide(const scene_view &sc, const ray_
         const uint32_t r23 = (c & 1u) ? ref[3] : ref[2];
         return (c & 2u) ? r23 : r01;
     };
-    st.push_if(k[3] != none, make_uint2(ref_of(k[3]), __float_as_uint(wide_key_tn(k[3]))));
-    st.push_if(k[2] != none, make_uint2(ref_of(k[2]), __float_as_uint(wide_key_tn(k[2]))));
-    st.push_if(k[1] != none, make_uint2(ref_of(k[1]), __float_as_uint(wide_key_tn(k[1]))));
-    if (k[0] != none) {
-        cur = ref_of(k[0]);
-        return true;
-    }
-    return st.pop(r.tmax, cur);
+#pragma unroll
+    for (int c = 3; c > 0; --c)
+        if (k[c] != none) st.push(stack_entry(ref_of(k[c]), wide_key_tn(k[c])));
+    if (k[0] != none) return ref_of(k[0]);
+    return st.template pop<kCulls>(r.tmax);
 }
 
 // One inner-node step: test both children's boxes; visit the nearer hit
 // child (ties -> child 0) and push the other if both are hit; with neither
-// hit, pop.  Returns false when the stack ran empty (ray finished).
-template <uint32_t kLayout = RT_LAYOUT_F32, class Isect, class Stack>
-__device__ __forceinline__ bool inner_step(const scene_view &sc, const ray_state &r, Isect &isect,
-                                           Stack &st, uint32_t &cur)
+// hit, pop.  Returns the reference to go on with: kNoRef when a sentinel was
+// popped (ray or nested traversal finished).
+template <bool kCulls, uint32_t kLayout = RT_LAYOUT_F32, class Isect, class Stack>
+__device__ __forceinline__ uint32_t inner_step(const scene_view &sc, const ray_state &r, Isect &isect,
+                                               Stack &st, uint32_t cur)
 {
-    if constexpr (kLayout == RT_LAYOUT_WIDE4) return inner_step_wide(sc, r, isect, st, cur);
+    if constexpr (kLayout == RT_LAYOUT_WIDE4)
+        return inner_step_wide<kCulls>(sc, r, isect, st, cur);
     float b[12];
     uint32_t ref0, ref1;
     node_children<kLayout>(sc, cur, b, ref0, ref1);
@@ -443,18 +493,18 @@ __device__ __forceinline__ bool inner_step(const scene_view &sc, const ray_state
     const uint32_t near = (hl && !(hr && right_first)) ? ref0 : ref1;
     const uint32_t far = right_first ? ref0 : ref1;
     const float far_tn = right_first ? tl : tr;
-    st.push_if(hl && hr, make_uint2(far, __float_as_uint(far_tn)));
-    if (hl || hr) {
-        cur = near;
-        return true;
-    }
-    return st.pop(r.tmax, cur);
+    if (hl && hr) st.push(stack_entry(far, far_tn));
+    uint32_t next = near;
+    if (!(hl || hr)) next = st.template pop<kCulls>(r.tmax);
+    return next;
 }
 
 // Result policies: what a query keeps of the accepted hits (Section 3.1).
 // commit() receives every accepted candidate in traversal order, may shrink
 // the search interval r.tmax, and returns true when the ray is finished.
+// kShrinks: commit() may lower r.tmax.
 struct closest_result {  // the nearest accepted hit
+    static constexpr bool kShrinks = true;
     float t, u, v;
     uint32_t prim;
     __device__ __forceinline__ void reset(const ray_state &, uint32_t)
@@ -476,6 +526,7 @@ struct closest_result {  // the nearest accepted hit
 };
 
 struct any_result {  // the first accepted hit met
+    static constexpr bool kShrinks = false;
     uint32_t prim;
     __device__ __forceinline__ void reset(const ray_state &, uint32_t) { prim = kMissPrim; }
     __device__ __forceinline__ bool commit(ray_state &, float, float, float, uint32_t p, uint32_t)
@@ -494,6 +545,7 @@ struct any_result {  // the first accepted hit met
 // the same ray give the same u, v), which halves the list's registers.
 template <int kMax>
 struct multi_result {
+    static constexpr bool kShrinks = true;
     float t[kMax];
     uint32_t rec[kMax];
     uint32_t n, k;
@@ -754,9 +806,12 @@ struct ray_feed {
     // Wave-wide after a successful refill: the idle lanes take the next rays
     // in lane order; a lane's ray id is valid iff it is below `end` (read
     // before the call).
-    __device__ __forceinline__ uint32_t take(uint64_t idle, uint64_t lanes_below)
+    __device__ __forceinline__ uint32_t take(uint64_t idle)
     {
-        const uint32_t id = next + uint32_t(__popcll(idle & lanes_below));
+        // idle lanes below this one
+        const uint32_t rank = __builtin_amdgcn_mbcnt_hi(
+            uint32_t(idle >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(idle), 0));
+        const uint32_t id = next + rank;
         next = min(next + uint32_t(__popcll(idle)), end);
         return id;
     }
@@ -764,21 +819,25 @@ struct ray_feed {
     __device__ __forceinline__ bool exhausted() const { return drained && next >= end; }
 };
 
-// A wave leaves its inner-node phase for the leaf phase once fewer than
-// kLeafBreak/16 of its busy lanes are still at inner nodes: waiting for the
-// last lane to reach a leaf would issue every node fetch for a few lanes.
-constexpr uint32_t kLeafBreak = 8;
-// Lane masks from compares: an LLVM integer-compare predicate code for
-// __builtin_amdgcn_uicmp (ne, unsigned less-than), the first reference of
-// a leaf (count 1 << 29: inner references are below it), and the key of a
-// finished lane.
-constexpr int kIcmpNE = 33, kIcmpULT = 36;
+// Lane masks from compares: LLVM integer-compare predicate codes for
+// __builtin_amdgcn_uicmp (eq, ne, unsigned less-than) and the first reference of
+// a leaf (count 1 << 29: inner references are below it).
+constexpr int kIcmpEQ = 32, kIcmpNE = 33, kIcmpULT = 36;
 constexpr uint32_t kRefCountUnit = 1u << 29;
-constexpr uint32_t kNoRef = 0xFFFFFFFFu;
 
-__device__ __forceinline__ bool leave_inner_phase(uint32_t n_inner, uint32_t n_leaf)
+// A wave stays in its inner-node phase while at least half of its busy lanes
+// are at inner nodes: waiting for the last lane to reach a leaf would issue
+// every node fetch for a few lanes.  (The masks straight from compares: a
+// ballot of a combined condition costs a select and a compare more each; the
+// counts through readfirstlane: kept as 64-bit values they are compared on the
+// vector unit.)
+__device__ __forceinline__ bool stay_in_inner_phase(uint32_t cur)
 {
-    return 16u * n_inner < kLeafBreak * (n_inner + n_leaf);
+    const uint32_t n_inner = __builtin_amdgcn_readfirstlane(
+        uint32_t(__popcll(__builtin_amdgcn_uicmp(cur, kRefCountUnit, kIcmpULT))));
+    const uint32_t n_busy = __builtin_amdgcn_readfirstlane(
+        uint32_t(__popcll(__builtin_amdgcn_uicmp(cur, kNoRef, kIcmpNE))));
+    return 2u * n_inner >= max(n_busy, 1u);
 }
 
 // Waves per SIMD a traversal kernel must fit.  The k <= 4 multi-hit list fits
@@ -800,18 +859,12 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(min_wave
 void trace_kernel(kernel_args a, typename Isect::params p)
 {
     static_assert(kBlock % 64 == 0 && kChunk % 32 == 0, "wave64 shapes");
-    __shared__ uint2 ring[kSlots][kBlock];
-    const uint32_t tid = threadIdx.x;
-    const uint32_t gtid = blockIdx.x * kBlock + tid;
-    const uint32_t lane = __lane_id();
-    const uint64_t lanes_below = (uint64_t(1) << lane) - 1;
+    __shared__ uint64_t ring[kSlots * kBlock];
+    ray_feed<kBlock, kChunk, kQueue> feed(a.n_rays, blockIdx.x * kBlock + threadIdx.x, a.order);
 
-    ray_feed<kBlock, kChunk, kQueue> feed(a.n_rays, gtid, a.order);
-
-    ring_stack<kSlots, kBlock> st{ring, (global_ptr<uint64_t>)(a.spill + gtid), tid,
-                                  gridDim.x * uint32_t(kBlock)};
-    bool active = false;
-    uint32_t ray_id = 0, cur = 0;
+    ring_stack<kSlots, kBlock> st(ring, a.spill);
+    // a lane without a ray has cur = kNoRef
+    uint32_t ray_id = 0, cur = kNoRef;
     ray_state r{};
     scene_view sc = a.sc;  // per lane in a batched launch
     Isect isect(p);
@@ -826,10 +879,10 @@ void trace_kernel(kernel_args a, typename Isect::params p)
     };
 
     for (;;) {
-        const uint64_t idle = __ballot(!active);
+        const uint64_t idle = __builtin_amdgcn_uicmp(cur, kNoRef, kIcmpEQ);
         if (feed.refill(idle, a.n_rays, a.queue, a.order)) {
-            const uint32_t id = feed.take(idle, lanes_below);
-            if (!active && id < feed.end) {
+            const uint32_t id = feed.take(idle);
+            if (cur == kNoRef && id < feed.end) {
                 ray_id = scheduled_ray(a, id);
                 r = make_ray(a.rays[2 * size_t(ray_id)], a.rays[2 * size_t(ray_id) + 1]);
                 if constexpr (kBatched) {
@@ -855,16 +908,17 @@ void trace_kernel(kernel_args a, typename Isect::params p)
                 }
                 st.reset();
                 res.reset(r, a.multi_k);
-                cur = sc.root_ref;
-                active = root_step(sc, r, isect);
-                if (!active) finish();
+                if (root_step(sc, r, isect))
+                    cur = sc.root_ref;
+                else
+                    finish();
             }
         }
-        if (__ballot(active) == 0) {
+        if (__builtin_amdgcn_uicmp(cur, kNoRef, kIcmpNE) == 0) {
             if (feed.exhausted()) break;
             continue;
         }
-        if (active) {
+        if (cur != kNoRef) {
             // inner phase: lanes at inner nodes step on while enough of them
             // remain; lanes already at a leaf wait (their ray's order is
             // unchanged -- a lane that leaves this phase at an inner node
@@ -874,29 +928,20 @@ void trace_kernel(kernel_args a, typename Isect::params p)
             // then issue ahead of the longer dependent leaf chains (measured
             // +2.6 % alpha billboards, +1.8 % spheres, default unchanged)
             __builtin_amdgcn_s_setprio(1);
-            for (;;) {
-                // the two lane masks straight from compares (a ballot of a
-                // combined condition costs a select and a compare more
-                // each): finished lanes carry the key kNoRef, which no
-                // reference equals (a leaf of 7 triangles at index 2^29 - 1
-                // would end past the largest triangle count)
-                const uint32_t key = active ? cur : kNoRef;
-                const uint64_t mi = __builtin_amdgcn_uicmp(key, kRefCountUnit, kIcmpULT);
-                if (mi == 0) break;
-                const uint64_t ml = __builtin_amdgcn_uicmp(key, kNoRef, kIcmpNE) & ~mi;
-                const bool in_inner = key < kRefCountUnit;
-                if (ml != 0 && leave_inner_phase(uint32_t(__popcll(mi)), uint32_t(__popcll(ml))))
-                    break;
-                if (in_inner && !inner_step<kLayout>(sc, r, isect, st, cur)) active = false;
+            if (stay_in_inner_phase(cur)) {
+                do {
+                    if (cur < kRefCountUnit)
+                        cur = inner_step<Result::kShrinks, kLayout>(sc, r, isect, st, cur);
+                } while (stay_in_inner_phase(cur));
             }
             __builtin_amdgcn_s_setprio(0);
-            if (active && ref_count(cur) != 0) {
+            if (cur >= kRefCountUnit && cur != kNoRef) {
                 if (leaf_step(sc, r, isect, cur, res))
-                    active = false;
+                    cur = kNoRef;
                 else
-                    active = st.pop(r.tmax, cur);
+                    cur = st.template pop<Result::kShrinks>(r.tmax);
             }
-            if (!active) finish();
+            if (cur == kNoRef) finish();
         }
     }
 }
@@ -924,18 +969,18 @@ __device__ __forceinline__ ray_state object_ray(const ray_state &w, const float 
 // boxes; its leaf records carry instance indices) is walked like any BVH; at
 // a top-level leaf each instance in stored order is entered by a full
 // traversal of its bottom-level BVH with the object ray, on the same stack
-// above a floor, sharing the distance bound; then the top level resumes.
+// above a sentinel, sharing the distance bound; then the top level resumes.
 template <class Isect, class Result, int kSlots>
 __global__ __launch_bounds__(64) void trace_instanced_kernel(kernel_args a, const unsigned char *table,
                                                              uint32_t *inst_out,
                                                              typename Isect::params p)
 {
-    __shared__ uint2 ring[kSlots][64];
-    const uint32_t tid = threadIdx.x;
-    const uint32_t pos = blockIdx.x * 64 + tid;
+    __shared__ uint64_t ring[kSlots * 64];
+    const uint32_t pos = blockIdx.x * 64 + threadIdx.x;
     if (pos >= a.n_rays) return;
     const uint32_t i = scheduled_ray(a, pos);  // tiled schedule, else pos
-    ring_stack<kSlots, 64> st{ring, (global_ptr<uint64_t>)(a.spill + pos), tid, gridDim.x * 64u};
+    ring_stack<kSlots, 64> st(ring, a.spill);
+    constexpr bool kCulls = Result::kShrinks;
     ray_state rw = make_ray(a.rays[2 * size_t(i)], a.rays[2 * size_t(i) + 1]);
     Isect isect(p);
     Result res;
@@ -948,16 +993,10 @@ __global__ __launch_bounds__(64) void trace_instanced_kernel(kernel_args a, cons
         reinterpret_cast<const instance_record *>(table + instance_records_offset(n_blas));
     const scene_view &tl = a.sc;
     bool done = false;
-    uint32_t cur = tl.root_ref;
-    bool alive = root_step(tl, rw, isect);
-    while (alive && !done) {
-        while (ref_count(cur) == 0) {
-            if (!inner_step(tl, rw, isect, st, cur)) {
-                alive = false;
-                break;
-            }
-        }
-        if (!alive) break;
+    uint32_t cur = root_step(tl, rw, isect) ? tl.root_ref : kNoRef;
+    while (cur != kNoRef && !done) {
+        while (cur < kRefCountUnit) cur = inner_step<kCulls>(tl, rw, isect, st, cur);
+        if (cur == kNoRef) break;
         const uint32_t first = ref_index(cur), count = ref_count(cur);
         for (uint32_t j = first; j < first + count && !done; ++j) {
             const uint32_t q = __float_as_uint(tl.tris[3 * size_t(j)].w);
@@ -985,31 +1024,24 @@ __global__ __launch_bounds__(64) void trace_instanced_kernel(kernel_args a, cons
             // the alpha mask reads the texture coordinates of the entered mesh
             if constexpr (std::is_base_of_v<alpha_intersector, Isect>) isect.p.texcoords = br.texcoords;
             const float t_before = ro.tmax;
-            st.floor = st.sp;
             if (root_step(bv, ro, isect)) {
+                st.push(kSentinel);
                 uint32_t c2 = bv.root_ref;
-                bool alive2 = true;
-                while (alive2) {
-                    while (ref_count(c2) == 0) {
-                        if (!inner_step(bv, ro, isect, st, c2)) {
-                            alive2 = false;
-                            break;
-                        }
-                    }
-                    if (!alive2) break;
+                while (c2 != kNoRef) {
+                    while (c2 < kRefCountUnit) c2 = inner_step<kCulls>(bv, ro, isect, st, c2);
+                    if (c2 == kNoRef) break;
                     if (leaf_step(bv, ro, isect, c2, res)) {
                         done = true;
                         break;
                     }
-                    alive2 = st.pop(ro.tmax, c2);
+                    c2 = st.template pop<kCulls>(ro.tmax);
                 }
             }
-            st.floor = 0;
             if (done || ro.tmax != t_before) inst_hit = q;
             rw.tmax = ro.tmax;
         }
         if (done) break;
-        alive = st.pop(rw.tmax, cur);
+        cur = st.template pop<kCulls>(rw.tmax);
     }
     write_result(a, tl, rw, i, res);
     if (inst_out) inst_out[i] = res_hit(res) ? inst_hit : kMissPrim;
