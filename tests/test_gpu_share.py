@@ -1,0 +1,83 @@
+"""Waves that share their last rays among idle lanes: the results are those of
+a lone lane per ray, bit for bit, also where hits tie across the shared
+pieces.  Every triangle comes three times, so that each hit ties twice, with
+the copies apart in the tree's leaves."""
+import numpy as np
+import pytest
+
+from paper_1912_12786_amd import workloads as W
+from tests import parity as P
+
+pytestmark = pytest.mark.gpu
+
+
+def announce(msg):
+    print(f"[gpu-case] {msg}", flush=True)
+
+
+@pytest.fixture(scope="module")
+def env():
+    import torch
+    assert torch.cuda.is_available()
+    from paper_1912_12786_amd import rtx
+    rtx.load_library()
+    return torch, rtx
+
+
+@pytest.fixture(scope="module")
+def scene(oracle_lib):
+    """400 triangles three times over, in mixed order, with random masks."""
+    rng = np.random.default_rng(11)
+    v = np.tile(W.random_triangles(400, 12, side=0.4), (3, 1, 1))[rng.permutation(1200)]
+    geom = rng.integers(0, 4, size=1200).astype(np.uint32)
+    tc = rng.uniform(0, 1, size=(1200, 3, 2)).astype(np.float32)
+    return v, geom, tc, W.alpha_textures(4, 64, 13), oracle_lib.build_bvh(v, max_leaf=1)
+
+
+# one ray, part of a wave, just over a wave, more chunks than the grid has waves
+@pytest.mark.parametrize("n_rays", [1, 40, 65, 5000, 700_000])
+@pytest.mark.parametrize("kind", ["default", "alpha", "procedural"])
+def test_shared_rays_equal_lone_rays(env, oracle_lib, scene, kind, n_rays):
+    torch, rtx = env
+    v, geom, tc, tex, bvh = scene
+    # scattered rays: long and short ones side by side in every wave
+    rays_np = W.incoherent_rays(n_rays, 21, box=(0.0, 1.0))
+    idx = np.arange(0, n_rays, max(1, n_rays // 20_000))
+    rays = torch.from_numpy(rays_np).cuda()
+    at = torch.from_numpy(idx).cuda()
+    okw = dict(geom_ids=geom, texcoords=tc, textures=tex) if kind == "alpha" else {}
+    for layout in ("f32", "q8", "f32p", "wide4"):
+        sc = rtx.upload_scene(v, geom, tc, tex, layout=layout, max_leaf=1)
+        for any_hit in (False, True):
+            B = oracle_lib.traverse(v, bvh, rays_np[idx], kind, any_hit=any_hit, layout=layout, **okw)
+            for shape in (None, (64, 8, 64, 0), (256, 8, 64, 1)):
+                announce(f"share {kind} {layout} any={any_hit} {shape} rays={n_rays}")
+                try:
+                    got = rtx.trace(sc, rays, kind, query="any" if any_hit else "closest",
+                                    shape=shape)
+                except rtx.RtxError as e:
+                    assert e.status == rtx.RT_ERR_UNSUPPORTED
+                    continue
+                torch.cuda.synchronize()
+                got = got[at]
+                if any_hit:
+                    assert np.array_equal(P.occluders_to_numpy(got), B["prim"])
+                else:
+                    P.assert_exact_vs_b(P.hits_to_numpy(got), B, f"share {kind} {layout}")
+
+
+@pytest.mark.parametrize("kind", ["default", "procedural", "alpha"])
+def test_shared_rays_of_a_batch(env, scene, kind):
+    """Waves whose lanes hold rays of different scenes."""
+    torch, rtx = env
+    v, geom, tc, tex, _ = scene
+    scenes = [rtx.upload_scene(x, geom[:len(x)], tc[:len(x)], tex, max_leaf=1)
+              for x in (v, v[:7], v[:300] * 0.5)]
+    counts = [3000, 30, 2001]
+    rays = [torch.from_numpy(W.incoherent_rays(n, 30 + i, box=(0.0, 1.0))).cuda()
+            for i, n in enumerate(counts)]
+    announce(f"share batch {kind}")
+    got = rtx.Batch(scenes, counts, kind).trace(torch.cat(rays))
+    one = torch.cat([rtx.trace(s, r, kind) for s, r in zip(scenes, rays)])
+    torch.cuda.synchronize()
+    assert torch.equal(got.view(torch.int32), one.view(torch.int32))
