@@ -140,8 +140,8 @@ typedef enum rt_isect_kind {
 /* Persistent-grid size, and so rays per lane, of launch shapes with a queue:
  * bits 28..31 of flags hold W, the most waves per SIMD the launch keeps
  * resident (1..15; 0 selects RT_DEFAULT_WAVES_PER_SIMD).  A queue launch
- * puts min(W, what the kernel's registers and LDS allow) waves on each of a
- * CU's 4 SIMDs (at least one block per CU), and its lanes take rays until the
+ * puts min(W, what the kernel's registers and LDS allow; 6 for the closest
+ * hit) waves on each of a CU's 4 SIMDs (at least one block per CU), and its lanes take rays until the
  * queue drains, so each lane traces n_rays / (64 x the grid's waves) rays on
  * average.  Fewer resident waves keep fewer rays' node paths in a CU's
  * caches at once.  Results and counters never depend on W; shapes without a

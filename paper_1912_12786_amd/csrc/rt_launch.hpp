@@ -119,7 +119,9 @@ rt_status launch_one(const kernel_args &a, const typename Isect::params &p, hipS
         grid = grid < resident ? grid : resident;
         const uint32_t cus = device_cus(err);
         if (cus == 0) return RT_ERR_HIP;
-        const uint32_t per_cu = 4 * waves_per_simd / uint32_t(kBlock / 64);
+        const uint32_t waves = waves_per_simd < max_waves_per_simd<Result>::value
+                                   ? waves_per_simd : max_waves_per_simd<Result>::value;
+        const uint32_t per_cu = 4 * waves / uint32_t(kBlock / 64);
         const uint32_t cap = cus * (per_cu > 0 ? per_cu : 1u);
         grid = grid < cap ? grid : cap;
         // A wave draws from the queue only after its static first chunk, and

@@ -779,76 +779,105 @@ __device__ __forceinline__ typename Isect::params batch_params(const typename Is
 // exhausted, from the others in turn.
 template <int kBlock, int kChunk, bool kQueue>
 struct ray_feed {
+    static constexpr uint32_t kAllHeads = (1u << kQueueHeads) - 1;
+    // all the same in every lane, and held in scalar registers: what is read
+    // from memory or changed in a loop goes through uniform()
     uint32_t next, end;
-    bool drained;  // no further chunk will come
-    uint32_t head, dead_heads;
+    uint32_t head, dead_heads;  // all heads dead: no further chunk will come
+    uint32_t base, row;         // chunks of 64: the chunk's ray j is base + (j / 8) row + j % 8
+
+    static __device__ __forceinline__ uint32_t uniform(uint32_t x)
+    {
+        return __builtin_amdgcn_readfirstlane(x);
+    }
 
     // The rays of the chunk at schedule position c (the chunk itself, or the
     // one a longest-path-first order puts there).
-    __device__ __forceinline__ void set_chunk(uint32_t c, uint32_t n_rays, const uint32_t *order)
+    __device__ __forceinline__ void set_chunk(uint32_t c, const kernel_args &a)
     {
-        if (order) c = __builtin_amdgcn_readfirstlane(order[c]);
+        if (a.order) c = uniform(a.order[c]);
         next = c * uint32_t(kChunk);
-        end = min(next + uint32_t(kChunk), n_rays);
+        end = min(next + uint32_t(kChunk), a.n_rays);
+        if constexpr (kChunk == 64) {
+            // a tile's place is worked out once per chunk (the integer division
+            // is 20 instructions), not for every lane of every refill
+            base = uniform(scheduled_ray(a, next));
+            row = next < a.tiled ? a.tile_w8 << 3 : 8u;
+        }
     }
 
-    __device__ __forceinline__ ray_feed(uint32_t n_rays, uint32_t gtid, const uint32_t *order)
+    // The ray at schedule position id of the current chunk.
+    __device__ __forceinline__ uint32_t ray(const kernel_args &a, uint32_t id) const
+    {
+        if constexpr (kChunk == 64) {
+            const uint32_t j = id & 63u;
+            return base + (j >> 3) * row + (j & 7u);
+        }
+        return scheduled_ray(a, id);
+    }
+
+    __device__ __forceinline__ ray_feed(const kernel_args &a, uint32_t gtid)
     {
         // every wave's first chunk is static (position = wave index), so a
         // queue launch does not start with every wave on an atomic
-        const uint32_t c = __builtin_amdgcn_readfirstlane(gtid / 64);
-        if (c * uint64_t(kChunk) < n_rays) {
-            set_chunk(c, n_rays, order);
-        } else {
-            next = end = 0;
-        }
-        drained = !kQueue;
+        const uint32_t c = uniform(gtid / 64);
+        next = end = base = row = 0;
+        if (c * uint64_t(kChunk) < a.n_rays) set_chunk(c, a);
         head = blockIdx.x % kQueueHeads;
-        dead_heads = 0;
+        // a grid with a wave for every chunk leaves nothing to draw: asking the
+        // eight heads in turn would cost eight dependent atomics at the end of
+        // every wave (4,096 rays 37.6 -> 35.2 us, 5,003 scattered rays 33.0 ->
+        // 29.7)
+        const bool none = !kQueue || uint64_t(gridDim.x) * (uint32_t(kBlock) / 64) * uint32_t(kChunk) >= a.n_rays;
+        dead_heads = none ? kAllHeads : 0u;
     }
 
-    // Wave-wide, with the wave's idle-lane mask: makes sure the chunk holds
-    // rays (drawing a new chunk from the queue if needed); false if none are
-    // left for now.
-    __device__ __forceinline__ bool refill(uint64_t idle, uint32_t n_rays, uint32_t *queue,
-                                          const uint32_t *order)
+    // Wave-wide: makes sure the chunk holds rays (drawing a new chunk from
+    // the queue if needed); false if none are left for now.  (Reading all
+    // heads at once to skip the exhausted ones was measured: the loads of the
+    // contended lines cost far more than the failing draws, 1080p alpha 440 ->
+    // 482 to 504 us.)
+    __device__ __forceinline__ bool refill(const kernel_args &a)
     {
         if constexpr (kQueue) {
-            if (idle != 0 && next >= end && !drained) {
-                const uint32_t n_chunks = (n_rays + uint32_t(kChunk) - 1) / uint32_t(kChunk);
-                const uint32_t first_dynamic = gridDim.x * (uint32_t(kBlock) / 64);
-                while (dead_heads != (1u << kQueueHeads) - 1) {
-                    uint32_t k = 0;
-                    if (__lane_id() == 0) k = atomicAdd(queue + head * kQueueStride, 1u);
-                    k = __builtin_amdgcn_readfirstlane(k);
-                    const uint64_t chunk = uint64_t(first_dynamic) + head + uint64_t(kQueueHeads) * k;
-                    if (chunk < n_chunks) {
-                        set_chunk(uint32_t(chunk), n_rays, order);
-                        break;
-                    }
+            const uint32_t n_chunks = (a.n_rays + uint32_t(kChunk) - 1) / uint32_t(kChunk);
+            const uint32_t first_dynamic = gridDim.x * (uint32_t(kBlock) / 64);
+            while (next >= end && dead_heads != kAllHeads) {
+                uint32_t k = 0;
+                if (__lane_id() == 0) k = atomicAdd(a.queue + head * kQueueStride, 1u);
+                k = uniform(k);
+                const uint64_t chunk = uint64_t(first_dynamic) + head + uint64_t(kQueueHeads) * k;
+                if (chunk < n_chunks) {
+                    set_chunk(uint32_t(chunk), a);
+                } else {
                     dead_heads |= 1u << head;
                     head = (head + 1) % kQueueHeads;
                 }
-                drained = dead_heads == (1u << kQueueHeads) - 1;
+                next = uniform(next);
+                end = uniform(end);
+                head = uniform(head);
+                dead_heads = uniform(dead_heads);
+                base = uniform(base);
+                row = uniform(row);
             }
         }
-        return idle != 0 && next < end;
+        return next < end;
     }
 
     // Wave-wide after a successful refill: the idle lanes take the next rays
     // in lane order; a lane's ray id is valid iff it is below `end` (read
     // before the call).
-    __device__ __forceinline__ uint32_t take(uint64_t idle)
+    __device__ __forceinline__ uint32_t take(uint64_t idle, uint32_t n_idle)
     {
         // idle lanes below this one
         const uint32_t rank = __builtin_amdgcn_mbcnt_hi(
             uint32_t(idle >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(idle), 0));
         const uint32_t id = next + rank;
-        next = min(next + uint32_t(__popcll(idle)), end);
+        next = uniform(min(next + n_idle, end));
         return id;
     }
 
-    __device__ __forceinline__ bool exhausted() const { return drained && next >= end; }
+    __device__ __forceinline__ bool exhausted() const { return dead_heads == kAllHeads && next >= end; }
 };
 
 // Lane masks from compares: LLVM integer-compare predicate codes for
@@ -884,6 +913,31 @@ template <>
 struct min_waves_per_simd<multi_result<4>> {
     static constexpr int value = 6;
 };
+
+// Most waves per SIMD of a persistent grid, where more fit.  The closest-hit
+// kernels fit 6 or 7 by registers (70 to 75) and 25 waves per CU by LDS; at 25
+// the spheres with bounce rays take 897 us against 842 at 24 (835 at 20) and
+// the default intersector at 720p 190 against 182 (175 at 20), more rays in
+// flight sharing the same L1, while the alpha mask and 32 scenes need the 24
+// (436 and 685 us, 460 and 746 at 20).  The any hit gains from a seventh wave:
+// 393 against 397 us.
+template <class Result>
+struct max_waves_per_simd {
+    static constexpr uint32_t value = 15;
+};
+template <>
+struct max_waves_per_simd<closest_result> {
+    static constexpr uint32_t value = 6;
+};
+
+// Idle lanes at which a wave with rays left to take refills them: a refill costs
+// the wave a round trip to memory and some 110 instructions whatever the number
+// of lanes, and rays started together share more nodes.  1 -> 16: 32 scenes in
+// one launch 732 -> 687 us, default intersector 184 -> 180, spheres 818 -> 811,
+// alpha any hit 401 -> 398, alpha closest 442 -> 440, heat map 331 -> 328; 24
+// gains another 1 to 2 % on the first two and loses 1.5 to 2 % on the alpha
+// mask, whose rays differ most in length.
+constexpr uint32_t kRefillAt = 16;
 
 // One round of a wave's lanes that have a ray: its inner-node phase, then one
 // leaf for every lane that has come to one.
@@ -1131,7 +1185,7 @@ void trace_kernel(kernel_args a, typename Isect::params p)
     constexpr bool kShares = is_stateless<Isect> && !(kBatched && std::is_same_v<Isect, alpha_intersector>) &&
                              (std::is_same_v<Result, closest_result> || std::is_same_v<Result, any_result>);
     __shared__ uint64_t ring[kSlots * kBlock];
-    ray_feed<kBlock, kChunk, kQueue> feed(a.n_rays, blockIdx.x * kBlock + threadIdx.x, a.order);
+    ray_feed<kBlock, kChunk, kQueue> feed(a, blockIdx.x * kBlock + threadIdx.x);
 
     ring_stack<kSlots, kBlock> st(ring, a.spill);
     // a lane without a ray has cur = kNoRef
@@ -1151,10 +1205,11 @@ void trace_kernel(kernel_args a, typename Isect::params p)
 
     for (;;) {
         const uint64_t idle = __builtin_amdgcn_uicmp(cur, kNoRef, kIcmpEQ);
-        if (feed.refill(idle, a.n_rays, a.queue, a.order)) {
-            const uint32_t id = feed.take(idle);
+        const uint32_t n_idle = __builtin_amdgcn_readfirstlane(uint32_t(__popcll(idle)));
+        if (n_idle >= kRefillAt && feed.refill(a)) {
+            const uint32_t id = feed.take(idle, n_idle);
             if (cur == kNoRef && id < feed.end) {
-                ray_id = scheduled_ray(a, id);
+                ray_id = feed.ray(a, id);
                 r = make_ray(a.rays[2 * size_t(ray_id)], a.rays[2 * size_t(ray_id) + 1]);
                 if constexpr (kBatched) {
                     const uint32_t n_scenes = *reinterpret_cast<const uint32_t *>(a.batch);
