@@ -74,6 +74,9 @@ struct LaunchShape {
 // drained and exit.
 constexpr uint64_t kPersistentWaves = 256 * 32;
 
+// Waves (4 per SIMD) that every kernel keeps resident at once.
+constexpr uint64_t kSplitWaves = 256 * 16;
+
 // Workspace layout: the queue heads in the first 1024 bytes (queue shapes:
 // 8 heads, 128 bytes apart), then the spill columns.
 constexpr size_t kQueueBytes = 1024;
@@ -99,6 +102,7 @@ struct TraceRequest {
     const void *batch;  // batched launch: device scene table (closest query), else null
     uint32_t runtime_dispatch;  // 0: compile-time intersector; 1: runtime switch; 2: indirect call
     void *spill;        // workspace past the queue head
+    size_t spill_bytes; // its size
     void *queue;        // queue head (queue shapes)
     LaunchShape shape;
     uint32_t tile_w8;   // tiled schedule: image width / 8 (0: index order)

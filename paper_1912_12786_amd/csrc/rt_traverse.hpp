@@ -690,6 +690,8 @@ struct kernel_args {
     uint32_t tile_w8;    // tiled schedule: image width / 8 (0: rays in index order)
     uint32_t tiled;      // rays [0, tiled) are whole rows of 8 x 8 tiles
     const uint32_t *order;  // longest-path-first: chunk to take at each position (else null)
+    uint32_t chunk;      // rays per chunk: the launch shape's, or a smaller power of two >= 8
+    uint64_t spill_threads;  // threads that the spill columns have room for (host only)
 };
 
 // The ray a lane takes for schedule position `pos`: in a tiled schedule,
@@ -784,7 +786,8 @@ struct ray_feed {
     // from memory or changed in a loop goes through uniform()
     uint32_t next, end;
     uint32_t head, dead_heads;  // all heads dead: no further chunk will come
-    uint32_t base, row;         // chunks of 64: the chunk's ray j is base + (j / 8) row + j % 8
+    // chunks of 64 or a part: ray j of the 64 that hold it is base + (j / 8) row + j % 8
+    uint32_t base, row;
 
     static __device__ __forceinline__ uint32_t uniform(uint32_t x)
     {
@@ -796,12 +799,12 @@ struct ray_feed {
     __device__ __forceinline__ void set_chunk(uint32_t c, const kernel_args &a)
     {
         if (a.order) c = uniform(a.order[c]);
-        next = c * uint32_t(kChunk);
-        end = min(next + uint32_t(kChunk), a.n_rays);
+        next = c * a.chunk;
+        end = min(next + a.chunk, a.n_rays);
         if constexpr (kChunk == 64) {
             // a tile's place is worked out once per chunk (the integer division
             // is 20 instructions), not for every lane of every refill
-            base = uniform(scheduled_ray(a, next));
+            base = uniform(scheduled_ray(a, next & ~63u));
             row = next < a.tiled ? a.tile_w8 << 3 : 8u;
         }
     }
@@ -822,13 +825,13 @@ struct ray_feed {
         // queue launch does not start with every wave on an atomic
         const uint32_t c = uniform(gtid / 64);
         next = end = base = row = 0;
-        if (c * uint64_t(kChunk) < a.n_rays) set_chunk(c, a);
+        if (c * uint64_t(a.chunk) < a.n_rays) set_chunk(c, a);
         head = blockIdx.x % kQueueHeads;
         // a grid with a wave for every chunk leaves nothing to draw: asking the
         // eight heads in turn would cost eight dependent atomics at the end of
         // every wave (4,096 rays 37.6 -> 35.2 us, 5,003 scattered rays 33.0 ->
         // 29.7)
-        const bool none = !kQueue || uint64_t(gridDim.x) * (uint32_t(kBlock) / 64) * uint32_t(kChunk) >= a.n_rays;
+        const bool none = !kQueue || uint64_t(gridDim.x) * (uint32_t(kBlock) / 64) * a.chunk >= a.n_rays;
         dead_heads = none ? kAllHeads : 0u;
     }
 
@@ -840,7 +843,7 @@ struct ray_feed {
     __device__ __forceinline__ bool refill(const kernel_args &a)
     {
         if constexpr (kQueue) {
-            const uint32_t n_chunks = (a.n_rays + uint32_t(kChunk) - 1) / uint32_t(kChunk);
+            const uint32_t n_chunks = uint32_t((uint64_t(a.n_rays) + a.chunk - 1) / a.chunk);
             const uint32_t first_dynamic = gridDim.x * (uint32_t(kBlock) / 64);
             while (next >= end && dead_heads != kAllHeads) {
                 uint32_t k = 0;
@@ -941,7 +944,9 @@ constexpr uint32_t kRefillAt = 16;
 
 // One round of a wave's lanes that have a ray: its inner-node phase, then one
 // leaf for every lane that has come to one.
-template <uint32_t kLayout, class Isect, class Stack, class Result>
+// kSteps > 0: after that many inner steps the round ends, without its leaf
+// phase, where the inner phase would go on.
+template <uint32_t kLayout, int kSteps = 0, class Isect, class Stack, class Result>
 __device__ __forceinline__ void traverse_round(const scene_view &sc, ray_state &r, Isect &isect,
                                                Stack &st, uint32_t &cur, Result &res)
 {
@@ -955,7 +960,12 @@ __device__ __forceinline__ void traverse_round(const scene_view &sc, ray_state &
     // +2.6 % alpha billboards, +1.8 % spheres, default unchanged)
     __builtin_amdgcn_s_setprio(1);
     if (stay_in_inner_phase(cur)) {
+        int steps = kSteps;
         do {
+            if (kSteps > 0 && steps-- == 0) {
+                __builtin_amdgcn_s_setprio(0);
+                return;
+            }
             if (cur < kRefCountUnit)
                 cur = inner_step<Result::kShrinks, kLayout>(sc, r, isect, st, cur);
         } while (stay_in_inner_phase(cur));
@@ -999,8 +1009,15 @@ __device__ __forceinline__ void traverse_round(const scene_view &sc, ray_state &
 // (727 k at 11 lanes -> 333 k at 25).  Thresholds of 4 to 16 idle lanes
 // measure the same within 1 %, 24 and 32 lose 0.5 to 2 %: a hand-over costs
 // about three inner steps.
+// While it shares, a wave looks for idle lanes every two inner steps: a ray
+// alone in its wave otherwise walks down to its first leaf before it gives
+// anything away (1,600 rays in 100 k billboards 60 -> 55 us, 9,216 rays 70 ->
+// 59, 40,000 rays 87 -> 75; 1080p alpha 436 -> 432; 512 x 512 rays, whose waves
+// begin full, 138 -> 143).  A count held at run time instead costs more than
+// it finds (40,000 rays 82).
 constexpr int kShareAt = 16;     // idle lanes at which a wave begins to share
 constexpr int kShareAgain = 16;  // idle lanes at which it hands out more
+constexpr int kShareSteps = 2;   // inner steps between two looks
 
 template <class Isect>
 constexpr bool is_stateless = std::is_same_v<Isect, default_intersector> ||
@@ -1168,7 +1185,7 @@ __device__ __forceinline__ void share_rest(const kernel_args &a, scene_view &sc,
             }
         }
         if (cur != kNoRef) {
-            traverse_round<kLayout>(sc, r, isect, st, cur, piece);
+            traverse_round<kLayout, kShareSteps>(sc, r, isect, st, cur, piece);
             if (cur != kNoRef && !piece.narrow(r)) cur = kNoRef;
         }
     }

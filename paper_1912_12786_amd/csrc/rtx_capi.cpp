@@ -234,6 +234,7 @@ rt_status trace_common(Query query, const rt_scene *scene, const rt_ray *rays, u
     q.order = longest_first ? w : nullptr;
     w += longest_first ? order_bytes(n_rays, shape) : 0;
     q.spill = w;
+    q.spill_bytes = workspace ? workspace_bytes - size_t(w - static_cast<char *>(workspace)) : 0;
     q.shape = shape;
     q.stream = stream;
     const char *err = "";

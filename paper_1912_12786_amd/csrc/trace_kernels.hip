@@ -262,13 +262,18 @@ rt_status launch_trace(const TraceRequest &q, const char **err)
     a.multi_k = q.multi_k;
     a.batch = static_cast<const unsigned char *>(q.batch);
     a.spill = static_cast<uint64_t *>(q.spill);
+    const uint32_t entries = spill_entries(q.scene->info, q.shape);
+    a.spill_threads = entries ? q.spill_bytes / (entries * sizeof(uint64_t)) : UINT64_MAX;
     a.queue = static_cast<uint32_t *>(q.queue);
     if (q.tile_w8) {  // whole rows of 8 x 8 tiles of an image 8 tile_w8 wide
         const uint64_t per_row = 64ull * q.tile_w8;
         a.tile_w8 = q.tile_w8;
         a.tiled = uint32_t(uint64_t(q.n_rays) / per_row * per_row);
     }
-    if (q.order) {  // longest-path-first: key and tally the chunks, then order them
+    // longest-path-first: key and tally the chunks, then order them -- unless
+    // all of them run at once, where an order changes nothing and its two
+    // launches would cost 10 us
+    if (q.order && (uint64_t(q.n_rays) + q.shape.chunk - 1) / q.shape.chunk > kSplitWaves) {
         static_assert(kOrderAreaBuckets == kOrderBuckets && kOrderAreaRowChunks == kOrderRowChunks,
                       "the chunk-order area's sizing and its kernels agree");
         const uint32_t chunk = q.shape.chunk;

@@ -41,6 +41,9 @@ RT_NODE_BYTES_F32P = 48
 RT_WIDE_EMPTY_REF = 0xFFFFFFFF
 RT_TRI_BYTES = 48
 RT_NOALLOC_SCRATCH_BYTES = 64 << 20
+# A Workspace's least size: the stacks of a small launch spread over 4,096 waves
+# take 2 MiB per tree level beyond the 8 held on chip
+WORKSPACE_MIN_BYTES = 32 << 20
 LAYOUTS = {"f32": 0, "q8": 1, "wide4": 2, "f32p": 3}
 KINDS = {"default": 0, "alpha": 1, "procedural": 2}
 
@@ -718,7 +721,8 @@ class Workspace:
         if nbytes == 0:
             return None, 0
         if self.buf is None or self.buf.numel() < nbytes:
-            self.buf = torch.empty(nbytes, dtype=torch.uint8, device=self.device)
+            self.buf = torch.empty(max(nbytes, WORKSPACE_MIN_BYTES), dtype=torch.uint8,
+                                   device=self.device)
         return self.buf.data_ptr(), int(self.buf.numel())
 
 

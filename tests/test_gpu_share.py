@@ -66,6 +66,40 @@ def test_shared_rays_equal_lone_rays(env, oracle_lib, scene, kind, n_rays):
                     P.assert_exact_vs_b(P.hits_to_numpy(got), B, f"share {kind} {layout}")
 
 
+# ray counts around the sizes where the rays per wave change (1, 2, 4, 8, 32, 64)
+@pytest.mark.parametrize("width,height", [(8, 1), (8, 511), (64, 64), (16, 257), (64, 129),
+                                          (128, 129), (512, 257), (512, 512), (520, 512)])
+@pytest.mark.parametrize("query", ["closest", "any", "multi", "count"])
+def test_rays_spread_over_more_waves(env, scene, width, height, query):
+    """Small launches give a wave fewer than 64 rays where the workspace has
+    room; shape (64, 8, 128, 1) never does.  Same bits, with and without
+    tiles and chunk order, and in a workspace of the least size."""
+    torch, rtx = env
+    v, geom, tc, tex, _ = scene
+    sc = rtx.upload_scene(v, geom, tc, tex, max_leaf=1)
+    rays = torch.from_numpy(W.pinhole_rays(width, height, np.array([0.5, 0.5, 2.5]),
+                                           np.full(3, 0.5), 40.0)).cuda()
+
+    class Least(rtx.Workspace):
+        def get(self, nbytes):
+            self.buf = torch.empty(max(nbytes, 16), dtype=torch.uint8, device="cuda")
+            return self.buf.data_ptr(), nbytes
+
+    def trace(**kw):
+        got = rtx.trace(sc, rays, "alpha", query="closest" if query == "count" else query, k=3,
+                        count=query == "count", **kw)
+        torch.cuda.synchronize()
+        return [x.view(torch.int32) for x in (got if isinstance(got, tuple) else (got,))]
+
+    want = trace(shape=(64, 8, 128, 1))
+    for shape in (None, (64, 8, 64, 0), (64, 16, 64, 1)):
+        for kw in ({}, {"image_width": width}, {"longest_first": True},
+                   {"image_width": width, "longest_first": True}, {"workspace": Least("cuda")}):
+            announce(f"spread {width}x{height} {query} {shape} {list(kw)}")
+            for a, b in zip(trace(shape=shape, **kw), want):
+                assert torch.equal(a, b)
+
+
 @pytest.mark.parametrize("kind", ["default", "procedural", "alpha"])
 def test_shared_rays_of_a_batch(env, scene, kind):
     """Waves whose lanes hold rays of different scenes."""
