@@ -562,6 +562,15 @@ rt_status rt_trace_multi(const rt_scene *scene, const rt_ray *rays, uint32_t n_r
                          rt_hit *hits, uint32_t *n_hits, rt_counters *counters, void *workspace,
                          size_t workspace_bytes, void *stream);
 
+/* The differentiable hit's forward outputs from its hit records, one
+ * pass: tuv[i] = (t, u, v), zeros for a miss; prim[i] = prim_id, -1 for a
+ * miss; hit[i] = 1 or 0.
+ *   hits  device, [n_rays] rt_hit, 16-byte aligned
+ *   tuv   device, [n_rays][3] float; prim device, [n_rays] int32; hit device,
+ *         [n_rays] uint8 */
+rt_status rt_hit_outputs(const rt_hit *hits, uint32_t n_rays, float *tuv, int32_t *prim,
+                         uint8_t *hit, void *stream);
+
 /* Adjoint of the accepted closest hits (differentiable hit).  For every ray
  * whose hit (from rt_trace_closest over the triangles vertices[faces]) is not
  * a miss, the hit point o + t d = (1-u-v) v0 + u v1 + v v2 of triangle

@@ -220,6 +220,10 @@ struct BackwardRequest {
     void *stream;
 };
 
+// Enqueues the split of hit records into (t, u, v), prim and hit flags.
+rt_status launch_hit_outputs(const void *hits, uint32_t n_rays, float *tuv, int32_t *prim,
+                             uint8_t *hit, void *stream, const char **err);
+
 // Enqueues the adjoint of the accepted hits; returns RT_OK or RT_ERR_HIP.
 rt_status launch_hit_backward(const BackwardRequest &req, const char **err);
 

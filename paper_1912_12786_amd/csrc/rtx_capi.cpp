@@ -793,6 +793,23 @@ rt_status rt_trace_multi(const rt_scene *scene, const rt_ray *rays, uint32_t n_r
                         counters, workspace, workspace_bytes, stream, k, n_hits);
 }
 
+rt_status rt_hit_outputs(const rt_hit *hits, uint32_t n_rays, float *tuv, int32_t *prim,
+                         uint8_t *hit, void *stream)
+{
+    g_last_error.clear();
+    if (n_rays == 0) return RT_OK;
+    if (n_rays > RT_MAX_RAYS) return fail(RT_ERR_INVALID_ARG, "more than 2^31 rays in one call");
+    if (!hits || !tuv || !prim || !hit)
+        return fail(RT_ERR_INVALID_ARG, "hits/tuv/prim/hit are NULL");
+    if (!aligned(hits, 16)) return fail(RT_ERR_MISALIGNED, "hits not 16-byte aligned");
+    if (!aligned(tuv, 4) || !aligned(prim, 4))
+        return fail(RT_ERR_MISALIGNED, "tuv and prim must be 4-byte aligned");
+    const char *err = "";
+    const rt_status st = launch_hit_outputs(hits, n_rays, tuv, prim, hit, stream, &err);
+    if (st != RT_OK) return fail(st, err);
+    return RT_OK;
+}
+
 rt_status rt_hit_backward(const rt_ray *rays, const rt_hit *hits, const float *grad_tuv,
                           uint32_t n_rays, const float *vertices, uint32_t n_vertices,
                           const uint32_t *faces, uint32_t n_tris, float *grad_vertices,

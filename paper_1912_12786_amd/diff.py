@@ -64,20 +64,26 @@ class DifferentiableHit(torch.autograd.Function):
                                      max_leaf=max_leaf)
         hits = rtx.trace(scene, rays.detach().contiguous(), intersector, alpha_min=alpha_min,
                          checker_n=checker_n, image_width=image_width, shape=shape)
-        prim = hits[:, 1].view(torch.int32).clone()
-        hit = prim != -1
-        tuv = hits[:, [0, 2, 3]].clone()
-        tuv[~hit] = 0.0
+        n = hits.shape[0]
+        tuv = torch.empty((n, 3), dtype=torch.float32, device=hits.device)
+        prim = torch.empty((n,), dtype=torch.int32, device=hits.device)
+        hit = torch.empty((n,), dtype=torch.bool, device=hits.device)
+        rtx.rt_hit_outputs(hits.data_ptr(), n, tuv.data_ptr(), prim.data_ptr(), hit.data_ptr(),
+                           torch.cuda.current_stream(hits.device).cuda_stream)
         # the backward kernel reads the faces on the vertices' device
         faces_u32 = f.to(device=v.device, dtype=torch.int32).contiguous()
         ctx.save_for_backward(rays.detach().contiguous(), hits, v.contiguous(), faces_u32)
         ctx.mark_non_differentiable(prim, hit)
+        # no gradients of prim and hit: backward would be handed zeros for them
+        ctx.set_materialize_grads(False)
         return tuv, prim, hit
 
     @staticmethod
     def backward(ctx, grad_tuv, grad_prim=None, grad_hit=None):
         rays, hits, vertices, faces = ctx.saved_tensors
         n = rays.shape[0]
+        if grad_tuv is None:
+            grad_tuv = torch.zeros((n, 3), dtype=torch.float32, device=rays.device)
         g = grad_tuv.contiguous().to(torch.float32)
         _same_cuda_device(rays=rays, hits=hits, vertices=vertices, faces=faces, grad_tuv=g)
         grad_vertices = torch.zeros_like(vertices)

@@ -138,6 +138,7 @@ SIGNATURES = [
                                      _U32, C.c_int, _P, _U32, C.c_int, _P, _P, _P, _P, _SZ, _P]),
     ("rt_trace_multi", C.c_int, [C.POINTER(rt_scene), _P, _U32, C.c_int, _P, _U32, _U32, _P, _P,
                                  _P, _P, _SZ, _P]),
+    ("rt_hit_outputs", C.c_int, [_P, _U32, _P, _P, _P, _P]),
     ("rt_hit_backward", C.c_int, [_P, _P, _P, _U32, _P, _U32, _P, _U32, _P, _P, _P]),
     ("rt_launch_shapes", C.c_uint32, [_P, _P, _P, _P, _U32]),
     ("rt_status_string", C.c_char_p, [C.c_int]),
@@ -444,6 +445,12 @@ def rt_trace_multi(scene: rt_scene, rays_ptr: int, n_rays: int, kind: int, param
                               None if params is None else C.cast(C.pointer(params), C.c_void_p),
                               flags, k, hits_ptr, n_hits_ptr, counters_ptr, workspace_ptr,
                               workspace_bytes, stream), "rt_trace_multi")
+
+
+def rt_hit_outputs(hits_ptr: int, n_rays: int, tuv_ptr: int, prim_ptr: int, hit_ptr: int,
+                   stream: int | None):
+    _check(load_library().rt_hit_outputs(hits_ptr, n_rays, tuv_ptr, prim_ptr, hit_ptr, stream),
+           "rt_hit_outputs")
 
 
 def rt_hit_backward(rays_ptr: int, hits_ptr: int, grad_tuv_ptr: int, n_rays: int,
