@@ -956,11 +956,13 @@ struct max_waves_per_simd<closest_result> {
 // Idle lanes at which a wave with rays left to take refills them: a refill costs
 // the wave a round trip to memory and some 110 instructions whatever the number
 // of lanes, and rays started together share more nodes.  1 -> 16: 32 scenes in
-// one launch 732 -> 687 us, default intersector 184 -> 180, spheres 818 -> 811,
-// alpha any hit 401 -> 398, alpha closest 442 -> 440, heat map 331 -> 328; 24
-// gains another 1 to 2 % on the first two and loses 1.5 to 2 % on the alpha
-// mask, whose rays differ most in length.
-constexpr uint32_t kRefillAt = 16;
+// one launch 732 -> 687 us, default intersector 184 -> 180, alpha any hit 401 ->
+// 398, alpha closest 442 -> 440.  16 -> 24: default intersector 179 -> 175,
+// spheres with a procedural mask 847 -> 826, 32 scenes 663 -> 650, but alpha
+// closest 434 -> 441 and any hit 387 -> 395: rays under the alpha mask differ
+// most in length, and more of their wave would wait.
+template <class Isect>
+constexpr uint32_t kRefillAt = std::is_base_of_v<alpha_intersector, Isect> ? 16 : 24;
 
 // One round of a wave's lanes that have a ray: its inner-node phase, then one
 // leaf for every lane that has come to one.
@@ -1277,7 +1279,7 @@ void trace_kernel(kernel_args a, typename Isect::params p)
     for (;;) {
         const uint64_t idle = __builtin_amdgcn_uicmp(cur, kNoRef, kIcmpEQ);
         const uint32_t n_idle = __builtin_amdgcn_readfirstlane(uint32_t(__popcll(idle)));
-        if (n_idle >= kRefillAt && feed.refill(a)) {
+        if (n_idle >= kRefillAt<Isect> && feed.refill(a)) {
             const uint32_t id = feed.take(idle, n_idle);
             if (cur == kNoRef && id < feed.end) {
                 ray_id = feed.ray(a, id);
