@@ -74,7 +74,7 @@ struct LaunchShape {
 // drained and exit.
 constexpr uint64_t kPersistentWaves = 256 * 32;
 
-// Waves (4 per SIMD) that every kernel keeps resident at once.
+// Waves (4 per SIMD) that the kernels keep resident at once (the 8 nearest hits: 3).
 constexpr uint64_t kSplitWaves = 256 * 16;
 
 // Workspace layout: the queue heads in the first 1024 bytes (queue shapes:

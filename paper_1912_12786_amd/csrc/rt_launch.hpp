@@ -102,21 +102,21 @@ inline kernel_args scene_args(const rt_scene &scene, const void *rays, uint32_t 
 }
 
 // Rays per chunk of a launch whose rays would leave most of the chip empty at
-// one wave per 64: halved as long as the waves stay within kSplitWaves (4 per
-// SIMD, which every kernel fits) and the spill columns have room for them.  The
-// waves then begin with few rays, and lanes without one take over parts of
-// them.  Kernel times at 64 rays per wave and split: 1,024 triangles, 4,096
-// rays 35 -> 21 us; billboards under the alpha mask, 1,600 rays 92 -> 55, 9,216
-// 99 -> 59, 40,000 112 -> 75, 102,400 129 -> 109; four nearest hits, which share
-// no rays, 1,600 113 -> 59, 40,000 144 -> 145; scattered rays on spheres, 2,500
-// 37 -> 30, 20,000 41 -> 39, 80,000 44 -> 44.  2,048 waves lose 5 to 15 % of that
-// at 9,216 to 102,400 rays, 8,192 lose 10 % on scattered rays.
-inline uint32_t split_chunk(const kernel_args &a)
+// one wave per 64: halved as long as the waves stay within max_waves
+// (kSplitWaves, or a queue launch's smaller cap) and the spill columns have room
+// for them.  The waves then begin with few rays, and lanes without one take
+// over parts of them.  Kernel times at 64 rays per wave and split: 1,024
+// triangles, 4,096 rays 35 -> 21 us; billboards under the alpha mask, 1,600 rays
+// 92 -> 55, 9,216 99 -> 59, 40,000 112 -> 75, 102,400 129 -> 109; four nearest
+// hits, which share no rays, 1,600 113 -> 59, 40,000 144 -> 145; scattered rays on
+// spheres, 2,500 37 -> 30, 20,000 41 -> 39, 80,000 44 -> 44.  2,048 waves lose 5
+// to 15 % of that at 9,216 to 102,400 rays, 8,192 lose 10 % on scattered rays.
+inline uint32_t split_chunk(const kernel_args &a, uint64_t max_waves)
 {
     uint32_t chunk = a.chunk;
     while (chunk > 1) {
         const uint64_t waves = (uint64_t(a.n_rays) + chunk / 2 - 1) / (chunk / 2);
-        if (waves > kSplitWaves || 64 * waves > a.spill_threads) break;
+        if (waves > max_waves || 64 * waves > a.spill_threads) break;
         chunk /= 2;
     }
     return chunk;
@@ -135,7 +135,9 @@ rt_status launch_one(kernel_args a, const typename Isect::params &p, hipStream_t
     // the workspace holds at least launch_threads(); a queue grid is further
     // trimmed to the waves that can be resident at once
     uint32_t grid = uint32_t(launch_threads(a.n_rays, sh) / kBlock);
-    if (kBlock == 64 && kChunk == 64 && a.order == nullptr) a.chunk = split_chunk(a);
+    if (kBlock == 64 && kChunk == 64 && a.order == nullptr)
+        a.chunk = split_chunk(a, kQueue && waves_per_simd < 4 ? kSplitWaves / 4 * waves_per_simd
+                                                              : kSplitWaves);
     if (a.chunk < kChunk) {  // a wave per chunk, and nothing for the queue
         grid = uint32_t((uint64_t(a.n_rays) + a.chunk - 1) / a.chunk);
     } else if constexpr (kQueue) {

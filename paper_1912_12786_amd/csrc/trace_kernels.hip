@@ -6,10 +6,10 @@
 // together.  The intersector is a template parameter, so its accept decision
 // and counters are inlined into the triangle loop (Section 3.2: the
 // intersect calls are replaced at compile time); the default intersector
-// compiles to no code.  The traversal stack keeps its top entries in LDS,
-// laid out [entry][lane] so that a wave's pushes and pops touch consecutive
-// 8-byte words; deeper entries go to a per-ray slice of the caller's
-// workspace.
+// compiles to no code.  The traversal stack keeps its top entry in registers
+// and the next ones in LDS, laid out [entry][lane] so that a wave's pushes and
+// pops touch consecutive 8-byte words; deeper entries go to a per-lane column
+// of the caller's workspace.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
