@@ -255,6 +255,9 @@ __device__ __forceinline__ bool triangle(const ray_state &r, float4 a, float4 b,
 // (a leaf of 7 triangles at index 2^29 - 1 would end past the largest
 // triangle count).
 constexpr uint32_t kNoRef = 0xFFFFFFFFu;
+// The reference of a lane that waits (see shared_result); no node or leaf has
+// it either.
+constexpr uint32_t kParked = 0xFFFFFFFEu;
 
 // A stack entry: the reference in the low word, the bits of tn in the high one
 // (one 64-bit value, so that an LDS read lands in the entry's own registers).
@@ -552,9 +555,11 @@ __device__ __forceinline__ uint32_t inner_step(const scene_view &sc, const ray_s
 // commit() receives every accepted candidate in traversal order, may shrink
 // the search interval r.tmax, and returns true when the ray is finished.
 // kShrinks: commit() may lower r.tmax.  kDeferLeaves: see traverse_round.
+// kWaits: a hit may have to wait, see shared_result.
 struct closest_result {  // the nearest accepted hit
     static constexpr bool kShrinks = true;
     static constexpr bool kDeferLeaves = false;
+    static constexpr bool kWaits = false;
     float t, u, v;
     uint32_t prim;
     __device__ __forceinline__ void reset(const ray_state &, uint32_t)
@@ -578,6 +583,7 @@ struct closest_result {  // the nearest accepted hit
 struct any_result {  // the first accepted hit met
     static constexpr bool kShrinks = false;
     static constexpr bool kDeferLeaves = false;
+    static constexpr bool kWaits = false;
     uint32_t prim;
     __device__ __forceinline__ void reset(const ray_state &, uint32_t) { prim = kMissPrim; }
     __device__ __forceinline__ bool commit(ray_state &, float, float, float, uint32_t p, uint32_t)
@@ -598,6 +604,7 @@ template <int kMax>
 struct multi_result {
     static constexpr bool kShrinks = true;
     static constexpr bool kDeferLeaves = true;
+    static constexpr bool kWaits = false;
     float t[kMax];
     uint32_t rec[kMax];
     uint32_t n, k;
@@ -644,7 +651,8 @@ struct multi_result {
 };
 
 // The triangles of one leaf, in stored order.  Returns true iff the result
-// policy finished the ray.
+// policy finished the ray.  (A leaf with a hit that has to wait is tested again
+// later: its other hits are in the bound by then.)
 template <class Result, class Isect>
 __device__ __forceinline__ bool leaf_step(const scene_view &sc, ray_state &r, Isect &isect,
                                           uint32_t ref, Result &res)
@@ -659,6 +667,7 @@ __device__ __forceinline__ bool leaf_step(const scene_view &sc, ray_state &r, Is
             bool ok = true;
             if constexpr (Isect::kFilters)
                 ok = isect.accept(hit_candidate{__float_as_uint(a.w), __float_as_uint(b.w), t, u, v});
+            if constexpr (Result::kWaits) ok = ok && !res.must_wait(r, ref, a, b, c, t);
             if (ok && res.commit(r, t, u, v, __float_as_uint(a.w), j)) return true;
         }
     }
@@ -1026,10 +1035,17 @@ __device__ __forceinline__ void traverse_round(const scene_view &sc, ray_state &
     }
     __builtin_amdgcn_s_setprio(0);
     if (cur >= kRefCountUnit && cur != kNoRef) {
-        if (leaf_step(sc, r, isect, cur, res))
+        if (leaf_step(sc, r, isect, cur, res)) {
             cur = kNoRef;
-        else
-            cur = st.template pop<Result::kShrinks>(r.tmax);
+            return;
+        }
+        if constexpr (Result::kWaits) {
+            if (res.leaf != kNoRef) {
+                cur = kParked;
+                return;
+            }
+        }
+        cur = st.template pop<Result::kShrinks>(r.tmax);
     }
 }
 
@@ -1041,21 +1057,33 @@ __device__ __forceinline__ void traverse_round(const scene_view &sc, ray_state &
 // of 64 lanes busy.  From there on an idle lane takes over the bottom entry
 // -- the largest deferred subtree -- of a busy lane's stack, with that lane's
 // ray.  The pieces of a ray are ranked in the order in which a lone lane would
-// visit them, and the ray's result is what a lone lane would return:
-//   closest   the smallest t, of equal ones the first in rank: a lone lane
-//             keeps a hit until a strictly nearer one comes.  Every piece is
-//             searched with a bound no tighter than the lone lane's when it
-//             comes there (up to the first t reached so far, itself
-//             included), so every leaf that the lone lane visits is visited;
-//             a further leaf holds no nearer hit, since its box was entered
-//             beyond the bound.
-//   any       the accepted hit of the first piece in rank that has one; the
-//             bound never moves, so each piece is visited as by a lone lane.
-// (Lone lane and pieces can differ only where rounding puts a box's entry
-// beyond a hit inside it and the bound falls between the two; then the pieces
-// return the nearer hit.)  Not for counting (more nodes may be visited, about
-// 3 %), nor for intersectors that are not the library's own, which may keep
-// state per ray.
+// visit them, and the ray's result is what a lone lane would return, bit for
+// bit.
+//   any       The bound never moves, so each piece is visited as by a lone
+//             lane; the hit of the first piece in rank that has one.
+//   closest   A piece is bounded by its own hits and by those of earlier
+//             pieces, not of later ones: never tighter than a lone lane is
+//             there, so every node that the lone lane visits is visited.  It
+//             may visit further nodes, which the hits of an earlier piece
+//             would have culled.  A hit that lies beyond the entries of all
+//             boxes around it is the lone lane's whenever it is nearer than
+//             the lone lane's bound, as those boxes are then no reason to
+//             cull it; the smallest t of such hits, of equal ones the first
+//             in rank (a lone lane keeps a hit until a strictly nearer one
+//             comes), is the lone lane's.  But the slab and the triangle test
+//             round differently, and a hit can come out a rounding before its
+//             box: in an axis-aligned plane, whose boxes are flat, one in ten
+//             to four in ten do.  Whether the lone lane finds such a hit
+//             depends on its bound, so the piece waits there until all earlier
+//             ones are done; if their hits have moved the bound meanwhile, it
+//             starts again from its first node, now as a lone lane would.
+//             (must_wait() below compares a hit with the boxes around it.)
+// Where no plane is axis-aligned no piece waits.  Telling hits only to the
+// later pieces, and the comparison, cost the default intersector at 720p 176 ->
+// 182 us, 512 x 512 rays 3 us, the others 1 % or less against one bound for all
+// pieces, which now and then returned another of several coplanar triangles.
+// Not for counting (more nodes may be visited, about 3 %), nor for
+// intersectors that are not the library's own, which may keep state per ray.
 //
 // Measured on 1080p rays, before and after: alpha closest 469 -> 441 us, any
 // hit 441 -> 401, spheres with bounce rays 904 -> 818, 32 scenes 774 -> 730,
@@ -1078,6 +1106,25 @@ constexpr bool is_stateless = std::is_same_v<Isect, default_intersector> ||
                               std::is_same_v<Isect, alpha_intersector> ||
                               std::is_same_v<Isect, checker_intersector>;
 
+// Accesses to what other lanes of the wave write and read.
+template <class T>
+__device__ __forceinline__ T lds_load(const T *p)
+{
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+template <class T>
+__device__ __forceinline__ void lds_store(T *p, T v)
+{
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+template <class T>
+__device__ __forceinline__ void lds_min(T *p, T v)
+{
+    __hip_atomic_fetch_min(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
 // A ray's result while it is shared: one entry per lane that held a ray when
 // sharing began, in LDS, and for each lane the entry and rank of its piece.
 // Ranks: a piece owns [rank, end); one given away takes the upper half.
@@ -1088,56 +1135,136 @@ template <>
 struct shared_result<closest_result> {
     static constexpr bool kShrinks = true;
     static constexpr bool kDeferLeaves = false;
+    static constexpr bool kWaits = true;
     struct table {
-        uint64_t best;  // (ordered t, rank); rank 0: not from a shared piece
+        uint64_t best;   // (ordered t, rank); rank 0: not from a shared piece
         float t, u, v;
         uint32_t prim;
+        uint32_t first;  // the least rank of an unfinished piece, while one waits
     };
     table *entry;
     uint32_t rank;
+    uint64_t root;   // the piece's first stack entry; a sentinel once every earlier piece is done
+    float bound;     // what the ray and the earlier pieces' hits leave the piece
+    float begun;     // the bound that the piece began with
+    float told;      // r.tmax at the last settle()
+    uint32_t leaf = kNoRef;  // with a hit that the lone lane may have culled
 
+    // The piece that a lane has when sharing begins: its ray's first one.
+    __device__ __forceinline__ shared_result(table *e, const ray_state &r)
+        : entry(e), rank(1u), root(kSentinel), bound(r.tmax), begun(r.tmax), told(r.tmax)
+    {
+    }
+    // A piece taken over, with its giver's ray: r.tmax is the bound that all
+    // hits before this piece have set so far.
+    __device__ __forceinline__ void take(table *e, uint32_t rk, uint64_t node, const ray_state &r)
+    {
+        entry = e;
+        rank = rk;
+        root = node;
+        bound = begun = told = r.tmax;
+    }
+
+    // Distances ordered as integers.
     static __device__ __forceinline__ uint64_t key(float t, uint32_t rank)
     {
         const uint32_t b = __float_as_uint(t + 0.0f);  // -0 and 0 are equal
         return uint64_t((b & 0x80000000u) ? ~b : (b | 0x80000000u)) << 32 | rank;
     }
-    static __device__ __forceinline__ float t_of(uint64_t k)
-    {
-        const uint32_t b = uint32_t(k >> 32);
-        return __uint_as_float((b & 0x80000000u) ? (b & 0x7FFFFFFFu) : ~b);
-    }
     static __device__ __forceinline__ void begin(table &e, const ray_state &r)
     {
-        e.best = key(r.tmax, 0);
+        lds_store(&e.best, key(r.tmax, 0));
     }
-    // The bound that the other pieces' hits allow: the float after the
-    // smallest t, so that an equal one of an earlier piece is still found.
-    __device__ __forceinline__ bool narrow(ray_state &r) const
+    // Whether a ray can be shared: with a finite o/d no slab test meets a
+    // NaN, and entries never decrease from a box to one inside it.
+    static __device__ __forceinline__ bool divides(const ray_state &r)
     {
-        const uint64_t k = __hip_atomic_load(&entry->best, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        r.tmax = fminf(r.tmax, t_of(k + (uint64_t(1) << 32)));
-        return true;
+        return fabsf(r.bx) + fabsf(r.by) + fabsf(r.bz) < __builtin_huge_valf();
+    }
+
+    // Every box around the leaf holds the triangle's vertices, whatever the
+    // node layout, and the slab test's operations are monotone: along an axis
+    // no box's computed entry exceeds the least of fma(x, i, -b) over the
+    // vertices x.  Of these, v's is a; the others are a + e i but for the
+    // roundings of the edge, of the product and of a itself, each at most
+    // 2^-24 of its value.  (An edge of 0 is exact.)
+    static __device__ __forceinline__ float entry_bound(float v, float e1, float e2, float i, float b)
+    {
+        const float a = fmaf(v, i, -b);
+        const float m = fminf(fminf(e1 * i, e2 * i), 0.0f);
+        return m == 0.0f ? a : (a + m) + fmaf(fabsf(a) + fabsf(m), 0x1p-22f, 0x1p-140f);
+    }
+    __device__ __forceinline__ bool must_wait(const ray_state &r, uint32_t ref, float4 a, float4 b,
+                                              float4 c, float t)
+    {
+        const bool certain = uint32_t(root) == kNoRef ||
+                             (t >= entry_bound(a.x, b.x, c.x, r.ix, r.bx) &&
+                              t >= entry_bound(a.y, b.y, c.y, r.iy, r.by) &&
+                              t >= entry_bound(a.z, b.z, c.z, r.iz, r.bz));  // and t > tmin
+        if (!certain) leaf = ref;
+        return !certain;
     }
     __device__ __forceinline__ bool commit(ray_state &r, float t, float u, float v, uint32_t prim,
                                            uint32_t)
     {
         const uint64_t k = key(t, rank);
-        __hip_atomic_fetch_min(&entry->best, k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        lds_min(&entry->best, k);
         // of several lanes with hits of one ray, the one whose key is left
-        if (__hip_atomic_load(&entry->best, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) == k) {
-            entry->t = t;
-            entry->u = u;
-            entry->v = v;
-            entry->prim = prim;
+        if (lds_load(&entry->best) == k) {
+            lds_store(&entry->t, t);
+            lds_store(&entry->u, u);
+            lds_store(&entry->v, v);
+            lds_store(&entry->prim, prim);
         }
         r.tmax = t;
         return false;
     }
+
+    // Wave-wide after each round: tells the round's hits to the later pieces
+    // of their rays, and ends the waits of pieces whose earlier ones are done.
+    template <class Stack>
+    __device__ __forceinline__ void settle(ray_state &r, Stack &st, uint32_t &cur, uint32_t &given)
+    {
+        for (uint64_t hits = __ballot(r.tmax != told); hits != 0; hits &= hits - 1) {
+            const int l = __builtin_ctzll(hits);
+            const uint32_t at = uint32_t(uintptr_t(entry));  // (LDS: the low word tells)
+            const uint32_t e = __builtin_amdgcn_readlane(at, l);
+            const uint32_t k = __builtin_amdgcn_readlane(rank, l);
+            const float t = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(r.tmax), l));
+            if (at == e && rank > k && t < bound) {
+                bound = t;
+                if (t < r.tmax) {
+                    r.tmax = t;
+                    if (cur == kParked) {  // perhaps nothing to wait for any more
+                        cur = leaf;
+                        leaf = kNoRef;
+                    }
+                }
+            }
+        }
+        told = r.tmax;
+        if (__builtin_amdgcn_uicmp(cur, kParked, kIcmpEQ) != 0 && cur != kNoRef) {
+            lds_store(&entry->first, kNoRef);
+            lds_min(&entry->first, rank);
+            if (cur == kParked && lds_load(&entry->first) == rank) {
+                cur = leaf;
+                leaf = kNoRef;
+                if (bound != begun) {
+                    r.tmax = told = bound;
+                    st.reset();
+                    given = 0;
+                    cur = __uint_as_float(uint32_t(root >> 32)) > bound ? kNoRef : uint32_t(root);
+                }
+                root = kSentinel;
+            }
+        }
+    }
     static __device__ __forceinline__ void finish(const kernel_args &a, const table &e, uint32_t ray)
     {
-        if (uint32_t(e.best) != 0)
+        if (uint32_t(lds_load(&e.best)) != 0)
             static_cast<float4 *>(a.out)[ray] =
-                make_float4(e.t, __uint_as_float(e.prim), e.u, e.v);
+                make_float4(lds_load(&e.t), __uint_as_float(lds_load(&e.prim)), lds_load(&e.u),
+                            lds_load(&e.v));
     }
 };
 
@@ -1145,28 +1272,36 @@ template <>
 struct shared_result<any_result> {
     static constexpr bool kShrinks = false;
     static constexpr bool kDeferLeaves = false;
+    static constexpr bool kWaits = false;
     struct table {
         uint32_t best, prim;  // the first rank with a hit; kNoRef: none
     };
     table *entry;
     uint32_t rank;
 
-    static __device__ __forceinline__ void begin(table &e, const ray_state &) { e.best = kNoRef; }
-    // False once an earlier piece has a hit.
-    __device__ __forceinline__ bool narrow(ray_state &) const
+    __device__ __forceinline__ shared_result(table *e, const ray_state &) : entry(e), rank(1u) {}
+    __device__ __forceinline__ void take(table *e, uint32_t rk, uint64_t, const ray_state &)
     {
-        return __hip_atomic_load(&entry->best, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) > rank;
+        entry = e;
+        rank = rk;
     }
+    static __device__ __forceinline__ void begin(table &e, const ray_state &) { lds_store(&e.best, kNoRef); }
+    static __device__ __forceinline__ bool divides(const ray_state &) { return true; }
     __device__ __forceinline__ bool commit(ray_state &, float, float, float, uint32_t prim, uint32_t)
     {
-        __hip_atomic_fetch_min(&entry->best, rank, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        if (__hip_atomic_load(&entry->best, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) == rank)
-            entry->prim = prim;
+        lds_min(&entry->best, rank);
+        if (lds_load(&entry->best) == rank) lds_store(&entry->prim, prim);
         return true;
+    }
+    // Ends a piece once an earlier one has a hit.
+    template <class Stack>
+    __device__ __forceinline__ void settle(ray_state &, Stack &, uint32_t &cur, uint32_t &)
+    {
+        if (cur != kNoRef && lds_load(&entry->best) <= rank) cur = kNoRef;
     }
     static __device__ __forceinline__ void finish(const kernel_args &a, const table &e, uint32_t ray)
     {
-        if (e.best != kNoRef) static_cast<uint32_t *>(a.out)[ray] = e.prim;
+        if (lds_load(&e.best) != kNoRef) static_cast<uint32_t *>(a.out)[ray] = lds_load(&e.prim);
     }
 };
 
@@ -1195,8 +1330,8 @@ __device__ __forceinline__ void share_rest(const kernel_args &a, scene_view &sc,
         write_result(a, sc, r, ray_id, res);
         shared_result<Result>::begin(shared[lane], r);
     }
-    shared_result<Result> piece{shared + lane, 1u};
-    uint32_t end = kNoRef, given = 0;
+    shared_result<Result> piece(shared + lane, r);
+    uint32_t end = shared_result<Result>::divides(r) ? kNoRef : piece.rank + 1, given = 0;
     for (;;) {
         const uint64_t idle = __builtin_amdgcn_uicmp(cur, kNoRef, kIcmpEQ);
         if (idle == ~uint64_t(0)) break;
@@ -1230,8 +1365,7 @@ __device__ __forceinline__ void share_rest(const kernel_args &a, scene_view &sc,
                     sc.tris = from_lane(sc.tris, from);
                 }
                 if (takes) {
-                    piece.entry = shared + slot;
-                    piece.rank = first;
+                    piece.take(shared + slot, first, e, r);
                     end = last;
                     given = 0;
                     st.reset();
@@ -1240,10 +1374,8 @@ __device__ __forceinline__ void share_rest(const kernel_args &a, scene_view &sc,
                 }
             }
         }
-        if (cur != kNoRef) {
-            traverse_round<kLayout, kShareSteps>(sc, r, isect, st, cur, piece);
-            if (cur != kNoRef && !piece.narrow(r)) cur = kNoRef;
-        }
+        if (cur < kParked) traverse_round<kLayout, kShareSteps>(sc, r, isect, st, cur, piece);
+        piece.settle(r, st, cur, given);
     }
     if (owner) shared_result<Result>::finish(a, shared[lane], ray_id);
 }
