@@ -554,11 +554,10 @@ __device__ __forceinline__ uint32_t inner_step(const scene_view &sc, const ray_s
 // Result policies: what a query keeps of the accepted hits (Section 3.1).
 // commit() receives every accepted candidate in traversal order, may shrink
 // the search interval r.tmax, and returns true when the ray is finished.
-// kShrinks: commit() may lower r.tmax.  kDeferLeaves: see traverse_round.
-// kWaits: a hit may have to wait, see shared_result.
+// kShrinks: commit() may lower r.tmax.  kWaits: a hit may have to wait, see
+// shared_result.
 struct closest_result {  // the nearest accepted hit
     static constexpr bool kShrinks = true;
-    static constexpr bool kDeferLeaves = false;
     static constexpr bool kWaits = false;
     float t, u, v;
     uint32_t prim;
@@ -582,7 +581,6 @@ struct closest_result {  // the nearest accepted hit
 
 struct any_result {  // the first accepted hit met
     static constexpr bool kShrinks = false;
-    static constexpr bool kDeferLeaves = false;
     static constexpr bool kWaits = false;
     uint32_t prim;
     __device__ __forceinline__ void reset(const ray_state &, uint32_t) { prim = kMissPrim; }
@@ -603,7 +601,6 @@ struct any_result {  // the first accepted hit met
 template <int kMax>
 struct multi_result {
     static constexpr bool kShrinks = true;
-    static constexpr bool kDeferLeaves = true;
     static constexpr bool kWaits = false;
     float t[kMax];
     uint32_t rec[kMax];
@@ -975,6 +972,11 @@ constexpr uint32_t kRefillAt = std::is_base_of_v<alpha_intersector, Isect> ? 16 
 
 // One round of a wave's lanes that have a ray: its inner-node phase, then one
 // leaf for every lane that has come to one.
+// (A lane that walks on from its stack before its leaf is tested would gain the
+// k nearest hits under a mask 4 to 6 %, but its nodes are then culled by an
+// older bound than a lone lane's, and culling is not exact, see the sharing
+// below: of 16,384 rays on overlapping triangles in an axis-aligned plane some
+// kept another list.)
 // kSteps > 0: after that many inner steps the round ends, without its leaf
 // phase, where the inner phase would go on.
 template <uint32_t kLayout, int kSteps = 0, class Isect, class Stack, class Result>
@@ -990,38 +992,6 @@ __device__ __forceinline__ void traverse_round(const scene_view &sc, ray_state &
     // then issue ahead of the longer dependent leaf chains (measured
     // +2.6 % alpha billboards, +1.8 % spheres, default unchanged)
     __builtin_amdgcn_s_setprio(1);
-    // The k nearest hits under a mask go on past a leaf: the lane keeps the
-    // first leaf it comes to and walks on from its stack until the wave's leaf
-    // phase, so that more lanes have work in either phase.  Its later leaves
-    // are still tested later, with the bound that this one leaves; a node
-    // visited meanwhile that the bound would have spared holds no hit within
-    // it.  Alpha mask, 1000 x 562 rays, k = 4: 451 -> 432 us; 640 x 480, k = 8:
-    // 413 -> 387; procedural mask, 300 k scattered rays: 117 -> 114.  The others
-    // lose by it -- default intersector, k = 2 180 -> 184, k = 8 123 -> 125,
-    // alpha closest 441 -> 465, 5,003 scattered rays 33 -> 39 -- as their first
-    // hits end most of the walk, and counting rays visit exactly the nodes that
-    // they count.
-    if constexpr (Result::kDeferLeaves && Isect::kFilters && !Isect::kCounts) {
-        uint32_t leaf = kNoRef;
-        const uint32_t n_busy = __builtin_amdgcn_readfirstlane(uint32_t(__popcll(__ballot(true))));
-        if (cur >= kRefCountUnit) {  // come to in the last round
-            leaf = cur;
-            cur = st.template pop<Result::kShrinks>(r.tmax);
-        }
-        while (n_busy <= 2u * __builtin_amdgcn_readfirstlane(uint32_t(
-                             __popcll(__builtin_amdgcn_uicmp(cur, kRefCountUnit, kIcmpULT))))) {
-            if (cur < kRefCountUnit) {
-                cur = inner_step<Result::kShrinks, kLayout>(sc, r, isect, st, cur);
-                if (cur >= kRefCountUnit && cur != kNoRef && leaf == kNoRef) {
-                    leaf = cur;
-                    cur = st.template pop<Result::kShrinks>(r.tmax);
-                }
-            }
-        }
-        __builtin_amdgcn_s_setprio(0);
-        if (leaf != kNoRef && leaf_step(sc, r, isect, leaf, res)) cur = kNoRef;
-        return;
-    }
     if (stay_in_inner_phase(cur)) {
         int steps = kSteps;
         do {
@@ -1134,7 +1104,6 @@ struct shared_result;
 template <>
 struct shared_result<closest_result> {
     static constexpr bool kShrinks = true;
-    static constexpr bool kDeferLeaves = false;
     static constexpr bool kWaits = true;
     struct table {
         uint64_t best;   // (ordered t, rank); rank 0: not from a shared piece
@@ -1271,7 +1240,6 @@ struct shared_result<closest_result> {
 template <>
 struct shared_result<any_result> {
     static constexpr bool kShrinks = false;
-    static constexpr bool kDeferLeaves = false;
     static constexpr bool kWaits = false;
     struct table {
         uint32_t best, prim;  // the first rank with a hit; kNoRef: none

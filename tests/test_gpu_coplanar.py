@@ -132,3 +132,32 @@ def test_batch_in_one_plane(env, oracle_lib, kind):
         B = [oracle_lib.traverse(b[0], b[4], r, kind, layout=layout) for b, r in zip(built, rays_np)]
         P.assert_exact_vs_b(got, {k: np.concatenate([x[k] for x in B]) for k in ("t", "u", "v", "prim")},
                             f"batch {kind} {layout}")
+
+
+@pytest.mark.parametrize("k", [1, 2, 4, 5, 8])
+@pytest.mark.parametrize("name", list(SCENES))
+@pytest.mark.parametrize("kind", ["default", "procedural", "alpha"])
+def test_k_nearest_in_one_plane(env, oracle_lib, name, kind, k):
+    torch, rtx = env
+    v, geom, tc, tex, bvh = scene_of(oracle_lib, name)
+    okw = dict(geom_ids=geom, texcoords=tc, textures=tex) if kind == "alpha" else {}
+    for n_rays in (40, 5000, 128 * 128):
+        rays_np = rays_of(n_rays)
+        rays = torch.from_numpy(rays_np).cuda()
+        for layout in ("f32", "q8", "f32p", "wide4"):
+            sc = rtx.upload_scene(v, geom, tc, tex, layout=layout, max_leaf=1)
+            B = oracle_lib.traverse(v, bvh, rays_np, kind, layout=layout, multi_k=k, **okw)
+            for shape, kw in ways(torch, rtx, n_rays):
+                what = f"{name} {kind} {layout} k={k} {n_rays} rays {shape} {sorted(kw)}"
+                announce(what)
+                try:
+                    hits, n_hits = rtx.trace(sc, rays, kind, query="multi", k=k, shape=shape, **kw)
+                except rtx.RtxError as e:
+                    assert e.status == rtx.RT_ERR_UNSUPPORTED
+                    continue
+                torch.cuda.synchronize()
+                assert np.array_equal(n_hits.cpu().numpy().view(np.uint32), B["n_hits"]), what
+                h = hits.cpu().numpy()
+                assert np.array_equal(h[..., 1].view(np.uint32), B["prim"]), what
+                for c, key in ((0, "t"), (2, "u"), (3, "v")):
+                    assert np.array_equal(P.bits(h[..., c]), P.bits(B[key])), (what, key)
