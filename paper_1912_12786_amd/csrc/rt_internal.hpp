@@ -74,8 +74,11 @@ struct LaunchShape {
 // drained and exit.
 constexpr uint64_t kPersistentWaves = 256 * 32;
 
-// Waves (4 per SIMD) that the kernels keep resident at once (the 8 nearest hits: 3).
-constexpr uint64_t kSplitWaves = 256 * 16;
+// Waves per SIMD that every traversal kernel keeps resident (4 with the 8
+// nearest hits' registers or a ring of 16 slots; most keep 5 to 8), and the
+// waves of the whole chip at that.
+constexpr uint32_t kResidentWaves = 4;
+constexpr uint64_t kSplitWaves = 256 * 4 * kResidentWaves;
 
 // Workspace layout: the queue heads in the first 1024 bytes (queue shapes:
 // 8 heads, 128 bytes apart), then the spill columns.

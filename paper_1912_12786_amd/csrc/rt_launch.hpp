@@ -136,8 +136,8 @@ rt_status launch_one(kernel_args a, const typename Isect::params &p, hipStream_t
     // trimmed to the waves that can be resident at once
     uint32_t grid = uint32_t(launch_threads(a.n_rays, sh) / kBlock);
     if (kBlock == 64 && kChunk == 64 && a.order == nullptr)
-        a.chunk = split_chunk(a, kQueue && waves_per_simd < 4 ? kSplitWaves / 4 * waves_per_simd
-                                                              : kSplitWaves);
+        a.chunk = split_chunk(a, kQueue && waves_per_simd < kResidentWaves
+                                     ? kSplitWaves / kResidentWaves * waves_per_simd : kSplitWaves);
     if (a.chunk < kChunk) {  // a wave per chunk, and nothing for the queue
         grid = uint32_t((uint64_t(a.n_rays) + a.chunk - 1) / a.chunk);
     } else if constexpr (kQueue) {

@@ -272,8 +272,17 @@ rt_status launch_trace(const TraceRequest &q, const char **err)
     }
     // longest-path-first: key and tally the chunks, then order them -- unless
     // all of them run at once, where an order changes nothing and its two
-    // launches would cost 10 us
-    if (q.order && (uint64_t(q.n_rays) + q.shape.chunk - 1) / q.shape.chunk > kSplitWaves) {
+    // launches would cost 10 us: a wave per chunk, at the kResidentWaves per
+    // SIMD that every kernel keeps resident, or the fewer that a queue launch
+    // is held to
+    uint64_t at_once = UINT64_MAX;
+    if (q.order) {
+        const uint32_t cus = device_cus(err);
+        if (cus == 0) return RT_ERR_HIP;
+        at_once = uint64_t(cus) * 4 * (q.shape.queue && q.waves_per_simd < kResidentWaves
+                                           ? q.waves_per_simd : kResidentWaves);
+    }
+    if ((uint64_t(q.n_rays) + q.shape.chunk - 1) / q.shape.chunk > at_once) {
         static_assert(kOrderAreaBuckets == kOrderBuckets && kOrderAreaRowChunks == kOrderRowChunks,
                       "the chunk-order area's sizing and its kernels agree");
         const uint32_t chunk = q.shape.chunk;

@@ -258,3 +258,34 @@ def test_tiled_instanced_matches_index_order(env, kind):
                                     image_width=256)
             torch.cuda.synchronize()
             assert same_bits(got, ref) and torch.equal(gid, rid) and same_bits(gc, rc)
+
+
+@pytest.mark.parametrize("shape", [(64, 8, 64, 1), (64, 8, 32, 1), (64, 8, 128, 1), (64, 8, 64, 0)])
+@pytest.mark.parametrize("waves", [None, 1, 3])
+def test_longest_first_orders_what_does_not_run_at_once(env, billboards, shape, waves):
+    """The requested order is made as soon as one more chunk comes than the
+    launch keeps waves resident (4 per SIMD, or the waves asked for), with a
+    last chunk of one ray, of part of a chunk and whole; up to there nothing
+    is ordered.  The order area of the workspace tells."""
+    torch, rtx = env
+    wl, scenes, rays = billboards
+    chunk, queue = shape[2], shape[3]
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    at_once = cus * 4 * (min(waves or 4, 4) if queue else 4)
+    for n in (at_once * chunk, at_once * chunk + 1, at_once * chunk + chunk // 2 + 3,
+              (at_once + 1) * chunk):
+        announce(f"order of {n} rays, shape {shape}, {waves} waves per SIMD")
+        r = rays[:n].contiguous()
+        ws = rtx.Workspace("cuda")
+        ws.buf = torch.full((1 << 28,), 0x5A, dtype=torch.uint8, device="cuda")
+        got = rtx.trace(scenes["f32"], r, "alpha", alpha_min=128, shape=shape, longest_first=True,
+                        waves_per_simd=waves, workspace=ws)
+        ref = rtx.trace(scenes["f32"], r, "alpha", alpha_min=128, shape=shape, waves_per_simd=waves)
+        torch.cuda.synchronize()
+        assert same_bits(got, ref), (shape, n)
+        n_chunks = -(-n // chunk)
+        area = ws.buf[1024 * queue + 4 * n_chunks:][:4 * n_chunks].view(torch.int32)
+        if n_chunks > at_once:
+            assert torch.equal(area.sort().values.cpu(), torch.arange(n_chunks, dtype=torch.int32))
+        else:
+            assert (area == 0x5A5A5A5A).all()
