@@ -96,7 +96,9 @@ def default_build(workload: str, intersector, query: str):
 def find_counters(sha, workload, kind, query, layout, max_leaf, shape, ray_order,
                   schedule="index", order="index", waves=7):
     """The rocprofv3 counter record (``profiles/counters_*.json``) taken on
-    exactly this kernel source and configuration, or None."""
+    exactly this kernel source and configuration, or None.  (The library's
+    default grid answers to its own waves and to RT_DEFAULT_WAVES_PER_SIMD.)"""
+    from paper_1912_12786_amd import rtx
     if not os.path.isdir(PROFILES):
         return None
     for name in sorted(os.listdir(PROFILES)):
@@ -112,7 +114,8 @@ def find_counters(sha, workload, kind, query, layout, max_leaf, shape, ray_order
                 and cfg.get("ray_order", "scanline") == ray_order
                 and cfg.get("schedule", "index") == schedule
                 and cfg.get("order", "index") == order
-                and cfg.get("waves_per_simd") == waves):
+                and (cfg.get("waves_per_simd") == waves
+                     or (cfg.get("default_waves") and waves == rtx.RT_DEFAULT_WAVES_PER_SIMD))):
             rec["file"] = os.path.join("profiles", name)
             return rec
     return None
@@ -296,7 +299,7 @@ def ingest_counters(args, directory: str):
              + f" --layout {args.layout} --max-leaf {args.max_leaf}"
              + (f" --shape {args.shape}" if args.shape else "")
              + (f" --waves-per-simd {args.waves_per_simd}" if args.waves_per_simd else ""))
-    waves = args.waves_per_simd or rtx.RT_DEFAULT_WAVES_PER_SIMD
+    waves = args.waves_per_simd or rtx.default_waves("closest" if batched else args.query)
     base = f"python3 bench.py {flags} --steps {args.steps} --warmup {args.warmup} --no-cpu-baseline"
     pmc = "rocprofv3 --pmc {} --output-format csv -d <out>/{} -o bench -- "
     rec = {
@@ -304,7 +307,7 @@ def ingest_counters(args, directory: str):
         "config": {"workload": wl_name, "intersector": kind, "query": args.query,
                    "layout": args.layout, "max_leaf": args.max_leaf, "launch_shape": shape,
                    "ray_order": args.ray_order, "schedule": schedule, "order": order,
-                   "waves_per_simd": waves},
+                   "waves_per_simd": waves, "default_waves": args.waves_per_simd is None},
         "kernel": f"trace_kernel<{isect}, {res}{tail}",
         "dispatches": {"issue": issue["n"]},
         "ta_busy_frac": round(ta_busy, 4),
@@ -643,7 +646,7 @@ def bench_batched(args):
                    "node_layout": args.layout, "max_leaf": args.max_leaf,
                    "n_tris": int(sum(s["vertices"].shape[0] for s in scenes)), "n_rays": int(n),
                    "launch_shape": list(best),
-                   "waves_per_simd": args.waves_per_simd or rtx.RT_DEFAULT_WAVES_PER_SIMD},
+                   "waves_per_simd": args.waves_per_simd or rtx.default_waves()},
         "mrays_s": {k: round(n / v / 1e3, 2) for k, v in ms.items()},
         "ms": {k: round(v, 4) for k, v in ms.items()},
         "autotune_ms": tune_ms,
@@ -964,7 +967,7 @@ def main():
     counters_rec = find_counters(kernel_source_sha(), wl.name, kind, query, args.layout,
                                  args.max_leaf, list(shape or rtx.rt_launch_shapes()[0]),
                                  args.ray_order, "tiles" if width else "index", args.order,
-                                 args.waves_per_simd or rtx.RT_DEFAULT_WAVES_PER_SIMD)
+                                 args.waves_per_simd or rtx.default_waves(query))
 
     cpu = None
     if not args.no_cpu_baseline and query == "closest":
@@ -1013,7 +1016,7 @@ def main():
                                 args.layout, "64-B nodes, float32 child boxes"),
             "launch_shape": ([int(x) for x in args.shape.split(",")] if args.shape
                              else list(rtx.rt_launch_shapes()[0])),
-            "waves_per_simd": args.waves_per_simd or rtx.RT_DEFAULT_WAVES_PER_SIMD,
+            "waves_per_simd": args.waves_per_simd or rtx.default_waves(query),
         },
         "roofline": roofline(kernel_ms, alg_bytes, counters_rec) | {
             "kernel": f"trace_kernel<{kind}_intersector, {query}>",

@@ -124,20 +124,22 @@ inline uint32_t split_chunk(const kernel_args &a, uint64_t max_waves)
 
 // Enqueues one traversal kernel (and, for a queue shape, the reset of the
 // queue heads before it); returns RT_OK or RT_ERR_HIP.  A queue shape's grid
-// holds at most waves_per_simd waves per SIMD (4 SIMDs per CU).
+// holds at most waves_per_simd waves per SIMD (4 SIMDs per CU; 0: the query's
+// default).
 template <class Isect, class Result, int kSlots, int kBlock, int kChunk, bool kQueue,
           bool kBatched = false, uint32_t kLayout = RT_LAYOUT_F32>
 rt_status launch_one(kernel_args a, const typename Isect::params &p, hipStream_t s,
-                     const char **err, uint32_t waves_per_simd = RT_DEFAULT_WAVES_PER_SIMD)
+                     const char **err, uint32_t waves_per_simd = 0)
 {
+    const uint32_t waves = waves_per_simd ? waves_per_simd : default_waves_per_simd<Result>::value;
     const LaunchShape sh{kBlock, kSlots, kChunk, kQueue};
     auto kernel = trace_kernel<Isect, Result, kSlots, kBlock, kChunk, kQueue, kBatched, kLayout>;
     // the workspace holds at least launch_threads(); a queue grid is further
     // trimmed to the waves that can be resident at once
     uint32_t grid = uint32_t(launch_threads(a.n_rays, sh) / kBlock);
     if (kBlock == 64 && kChunk == 64 && a.order == nullptr)
-        a.chunk = split_chunk(a, kQueue && waves_per_simd < kResidentWaves
-                                     ? kSplitWaves / kResidentWaves * waves_per_simd : kSplitWaves);
+        a.chunk = split_chunk(a, kQueue && waves < kResidentWaves
+                                     ? kSplitWaves / kResidentWaves * waves : kSplitWaves);
     if (a.chunk < kChunk) {  // a wave per chunk, and nothing for the queue
         grid = uint32_t((uint64_t(a.n_rays) + a.chunk - 1) / a.chunk);
     } else if constexpr (kQueue) {
@@ -147,8 +149,6 @@ rt_status launch_one(kernel_args a, const typename Isect::params &p, hipStream_t
         grid = grid < resident ? grid : resident;
         const uint32_t cus = device_cus(err);
         if (cus == 0) return RT_ERR_HIP;
-        const uint32_t waves = waves_per_simd < max_waves_per_simd<Result>::value
-                                   ? waves_per_simd : max_waves_per_simd<Result>::value;
         const uint32_t per_cu = 4 * waves / uint32_t(kBlock / 64);
         const uint32_t cap = cus * (per_cu > 0 ? per_cu : 1u);
         grid = grid < cap ? grid : cap;

@@ -943,7 +943,7 @@ struct min_waves_per_simd<multi_result<4>> {
     static constexpr int value = 6;
 };
 
-// Most waves per SIMD of a persistent grid, where more fit.  The closest-hit
+// Waves per SIMD of a persistent grid where the caller names none.  The closest-hit
 // kernels fit 6 or 7 by registers (70 to 75) and 25 waves per CU by LDS; at 25
 // the spheres with bounce rays take 897 us against 842 at 24 (835 at 20) and
 // the default intersector at 720p 190 against 182 (175 at 20), more rays in
@@ -951,12 +951,12 @@ struct min_waves_per_simd<multi_result<4>> {
 // (436 and 685 us, 460 and 746 at 20).  The any hit gains from a seventh wave:
 // 393 against 397 us.
 template <class Result>
-struct max_waves_per_simd {
-    static constexpr uint32_t value = 15;
+struct default_waves_per_simd {
+    static constexpr uint32_t value = RT_DEFAULT_WAVES_PER_SIMD;
 };
 template <>
-struct max_waves_per_simd<closest_result> {
-    static constexpr uint32_t value = 6;
+struct default_waves_per_simd<closest_result> {
+    static constexpr uint32_t value = RT_DEFAULT_WAVES_CLOSEST;
 };
 
 // Idle lanes at which a wave with rays left to take refills them: a refill costs

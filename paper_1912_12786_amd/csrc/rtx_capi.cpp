@@ -167,8 +167,7 @@ rt_status trace_common(Query query, const rt_scene *scene, const rt_ray *rays, u
     TraceRequest q;
     q.runtime_dispatch = runtime == RT_FLAG_RUNTIME_SWITCH ? 1u : (runtime ? 2u : 0u);
     q.tile_w8 = (flags & RT_FLAG_TILE_MASK) >> RT_FLAG_TILE_SHIFT;
-    const uint32_t waves = (flags & RT_FLAG_WAVES_MASK) >> RT_FLAG_WAVES_SHIFT;
-    q.waves_per_simd = waves ? waves : RT_DEFAULT_WAVES_PER_SIMD;
+    q.waves_per_simd = (flags & RT_FLAG_WAVES_MASK) >> RT_FLAG_WAVES_SHIFT;
     if (q.tile_w8 && batch)
         return fail(RT_ERR_UNSUPPORTED, "the tiled schedule is for single-scene calls");
     const bool longest_first = (flags & RT_FLAG_LONGEST_FIRST) != 0;

@@ -279,8 +279,8 @@ rt_status launch_trace(const TraceRequest &q, const char **err)
     if (q.order) {
         const uint32_t cus = device_cus(err);
         if (cus == 0) return RT_ERR_HIP;
-        at_once = uint64_t(cus) * 4 * (q.shape.queue && q.waves_per_simd < kResidentWaves
-                                           ? q.waves_per_simd : kResidentWaves);
+        const bool fewer = q.shape.queue && q.waves_per_simd != 0 && q.waves_per_simd < kResidentWaves;
+        at_once = uint64_t(cus) * 4 * (fewer ? q.waves_per_simd : kResidentWaves);
     }
     if ((uint64_t(q.n_rays) + q.shape.chunk - 1) / q.shape.chunk > at_once) {
         static_assert(kOrderAreaBuckets == kOrderBuckets && kOrderAreaRowChunks == kOrderRowChunks,

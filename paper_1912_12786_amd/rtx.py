@@ -33,7 +33,8 @@ RT_FLAG_TILE_SHIFT = 16
 RT_FLAG_TILE_MASK = 0x0FFF0000
 RT_FLAG_WAVES_SHIFT = 28
 RT_FLAG_WAVES_MASK = 0xF0000000
-RT_DEFAULT_WAVES_PER_SIMD = 7
+RT_DEFAULT_WAVES_PER_SIMD = 7   # any hit, k nearest
+RT_DEFAULT_WAVES_CLOSEST = 6    # closest hit, batches
 RT_NODE_BYTES = 64
 RT_NODE_BYTES_Q8 = 32
 RT_NODE_BYTES_WIDE4 = 128
@@ -745,12 +746,17 @@ def tile_flag(image_width: int | None) -> int:
 
 def waves_flag(waves_per_simd: int | None) -> int:
     """Flag bits capping a queue launch's persistent grid at this many waves
-    per SIMD (1..15; None or 0: the library default, 7)."""
+    per SIMD (1..15; None or 0: the query's default, see :func:`default_waves`)."""
     if not waves_per_simd:
         return 0
     if not 1 <= int(waves_per_simd) <= 15:
         raise ValueError("waves per SIMD must be within 1..15")
     return int(waves_per_simd) << RT_FLAG_WAVES_SHIFT
+
+
+def default_waves(query: str = "closest") -> int:
+    """Waves per SIMD of a queue launch of this query that names none."""
+    return RT_DEFAULT_WAVES_CLOSEST if query == "closest" else RT_DEFAULT_WAVES_PER_SIMD
 
 
 def trace(scene: Scene, rays, intersector: str = "default", *, query: str = "closest",
@@ -774,7 +780,8 @@ def trace(scene: Scene, rays, intersector: str = "default", *, query: str = "clo
     that cross the most scene first (same results, see
     ``RT_FLAG_LONGEST_FIRST``).  ``waves_per_simd``: most resident waves per
     SIMD of a queue shape's persistent grid, which sets the rays per lane
-    (same results, see ``RT_FLAG_WAVES_PER_SIMD``; None: the default, 7)."""
+    (same results, see ``RT_FLAG_WAVES_PER_SIMD``; None: the default, 6 for the
+    closest hit and 7 for the others)."""
     torch = _torch()
     if rays.dtype != torch.float32 or rays.dim() != 2 or rays.shape[1] != 8 or not rays.is_contiguous():
         raise ValueError("rays must be a contiguous float32 [N, 8] tensor")

@@ -289,3 +289,29 @@ def test_longest_first_orders_what_does_not_run_at_once(env, billboards, shape, 
             assert torch.equal(area.sort().values.cpu(), torch.arange(n_chunks, dtype=torch.int32))
         else:
             assert (area == 0x5A5A5A5A).all()
+
+
+def test_waves_per_simd_is_what_was_asked_for(env, billboards):
+    """The grid of a queue launch: every wave ends when it has found each of
+    the 8 heads exhausted, so the heads end at (chunks drawn) + 8 per wave in
+    all, where chunks drawn = chunks - waves."""
+    torch, rtx = env
+    _, scenes, rays = billboards
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    n_chunks = -(-rays.shape[0] // 64)
+
+    def grid(query, waves):
+        announce(f"grid of {query}, {waves} waves per SIMD")
+        ws = rtx.Workspace("cuda")
+        rtx.trace(scenes["f32"], rays, "default", query=query, waves_per_simd=waves, workspace=ws)
+        torch.cuda.synchronize()
+        heads = ws.buf[:1024].view(torch.int32)[::32]
+        return (int(heads.sum()) - n_chunks) / 7
+
+    for w in (1, 4, 6):
+        assert grid("closest", w) == grid("any", w) == 4 * w * cus
+    # the kernels fit more than 6
+    assert grid("closest", 7) == grid("closest", 8) > 4 * 6 * cus
+    assert grid("any", 8) > grid("any", 7) == 4 * 7 * cus
+    assert grid("closest", None) == 4 * 6 * cus
+    assert grid("any", None) == 4 * 7 * cus
