@@ -42,9 +42,11 @@ RT_NODE_BYTES_F32P = 48
 RT_WIDE_EMPTY_REF = 0xFFFFFFFF
 RT_TRI_BYTES = 48
 RT_NOALLOC_SCRATCH_BYTES = 64 << 20
-# A Workspace's least size: the stacks of a small launch spread over 4,096 waves
-# take 2 MiB per tree level beyond the 8 held on chip
-WORKSPACE_MIN_BYTES = 32 << 20
+# A launch of fewer rays than this many spreads them over up to 4,096 waves if the
+# workspace holds those waves' stacks (2 MiB per tree level beyond those held on
+# chip); a Workspace grows for it by itself up to SPREAD_BYTES
+SPREAD_RAYS = 64 * 4096
+SPREAD_BYTES = 32 << 20
 LAYOUTS = {"f32": 0, "q8": 1, "wide4": 2, "f32p": 3}
 KINDS = {"default": 0, "alpha": 1, "procedural": 2}
 
@@ -723,14 +725,26 @@ class Workspace:
     def __init__(self, device="cuda"):
         self.device = device
         self.buf = None
+        self._spread = None
+
+    def make_room(self, depth: int, flags: int, nbytes):
+        """Room for spreading a small launch over a tree of this stack depth:
+        ``nbytes()`` is the size that SPREAD_RAYS rays need."""
+        key = (depth, flags & (RT_FLAG_SHAPE_MASK | RT_FLAG_LONGEST_FIRST))
+        if key == self._spread:
+            return
+        self._spread = key
+        shape = (flags & RT_FLAG_SHAPE_MASK) >> RT_FLAG_SHAPE_SHIFT
+        # the launch shapes that spread, the default (0) among them
+        if shape == 0 or rt_launch_shapes()[shape][0::2] == (64, 64):
+            self.get(min(nbytes(), SPREAD_BYTES))
 
     def get(self, nbytes: int):
         torch = _torch()
         if nbytes == 0:
             return None, 0
         if self.buf is None or self.buf.numel() < nbytes:
-            self.buf = torch.empty(max(nbytes, WORKSPACE_MIN_BYTES), dtype=torch.uint8,
-                                   device=self.device)
+            self.buf = torch.empty(nbytes, dtype=torch.uint8, device=self.device)
         return self.buf.data_ptr(), int(self.buf.numel())
 
 
@@ -815,7 +829,11 @@ def _trace_on(scene, rays, intersector, query, count, alpha_min, checker_n, k, o
     if count and counters is None:
         counters = torch.empty((n, 4), dtype=torch.int32, device=dev)
     ws = workspace or Workspace(dev)
-    wptr, wbytes = ws.get(rt_trace_workspace_bytes(sc, n, flags))
+    need = rt_trace_workspace_bytes(sc, n, flags)
+    if need and n < SPREAD_RAYS and isinstance(ws, Workspace):
+        ws.make_room(int(sc.info.max_depth), flags,
+                     lambda: rt_trace_workspace_bytes(sc, SPREAD_RAYS, flags))
+    wptr, wbytes = ws.get(need)
     cptr = counters.data_ptr() if count else None
     if query == "closest":
         rt_trace_closest(sc, rays.data_ptr(), n, KINDS[intersector], params, flags,
@@ -854,6 +872,11 @@ class Batch:
         self.table = torch.from_numpy(table.copy()).to(device)
         self.offsets = np.concatenate([[0], np.cumsum(np.asarray(n_rays, np.int64))])
 
+    def _spread_bytes(self, flags):
+        info = rt_batch_info.from_buffer_copy(self.info)
+        info.n_rays = SPREAD_RAYS
+        return rt_trace_batch_workspace_bytes(info, flags)
+
     def trace(self, rays, *, count=False, checker_n: int = 8, out=None, counters=None,
               workspace: Workspace | None = None, stream=None, shape=None,
               waves_per_simd: int | None = None):
@@ -882,7 +905,10 @@ class Batch:
             params = rt_procedural_params()
             params.checker_n = int(checker_n)
         ws = workspace or Workspace(dev)
-        wptr, wbytes = ws.get(rt_trace_batch_workspace_bytes(self.info, flags))
+        need = rt_trace_batch_workspace_bytes(self.info, flags)
+        if need and n < SPREAD_RAYS and isinstance(ws, Workspace):
+            ws.make_room(int(self.info.max_depth), flags, lambda: self._spread_bytes(flags))
+        wptr, wbytes = ws.get(need)
         rt_trace_batch(self.table.data_ptr(), self.info, rays.data_ptr(), self.kind, params, flags,
                        out.data_ptr(), counters.data_ptr() if count else None, wptr, wbytes, s)
         return (out, counters) if count else out

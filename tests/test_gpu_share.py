@@ -115,3 +115,26 @@ def test_shared_rays_of_a_batch(env, scene, kind):
     one = torch.cat([rtx.trace(s, r, kind) for s, r in zip(scenes, rays)])
     torch.cuda.synchronize()
     assert torch.equal(got.view(torch.int32), one.view(torch.int32))
+
+
+@pytest.mark.parametrize("n_rays", [1, 5000, 64 * 4096 - 1, 64 * 4096])
+def test_workspace_of_a_small_launch(env, scene, n_rays):
+    """A program's workspace grows to what spreading a small launch takes, in
+    calls that spread, and no further."""
+    torch, rtx = env
+    v, geom, tc, tex, _ = scene
+    sc = rtx.upload_scene(v, geom, tc, tex, max_leaf=1)
+    rays = torch.from_numpy(W.incoherent_rays(n_rays, 3, box=(0.0, 1.0))).cuda()
+    announce(f"workspace of {n_rays} rays, depth {sc.info.max_depth}")
+    full = rtx.rt_trace_workspace_bytes(sc.view, rtx.SPREAD_RAYS, 0)
+    ws = rtx.Workspace("cuda")
+    rtx.trace(sc, rays, workspace=ws)
+    assert ws.buf.numel() == full > 1024
+    batch = rtx.Batch([sc], [n_rays])
+    ws = rtx.Workspace("cuda")
+    batch.trace(rays, workspace=ws)
+    assert ws.buf.numel() == full
+    ws = rtx.Workspace("cuda")
+    rtx.trace(sc, rays, workspace=ws, shape=(256, 8, 64, 1))
+    assert ws.buf.numel() == rtx.rt_trace_workspace_bytes(sc.view, n_rays, rtx.shape_flag((256, 8, 64, 1)))
+    torch.cuda.synchronize()
