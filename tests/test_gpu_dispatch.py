@@ -60,3 +60,30 @@ def test_runtime_dispatch_is_bit_identical(oracle_lib, workload, kind):
                             count=False, **okw)
     from tests import parity as P
     P.assert_exact_vs_b(P.hits_to_numpy(ref), B, f"dispatch {workload} {kind}")
+
+
+def test_switch_runs_in_the_same_kernel_otherwise():
+    """Compile time against run time compares the dispatch alone: the switch's
+    kernel shares and refills rays like the compiled-in mask's, so at 1080p the
+    two differ by a few percent (1 % measured; 18 % when only the compiled-in
+    mask shared its last rays).  Least of five rounds in turn."""
+    import bench
+    import torch
+    from paper_1912_12786_amd import rtx
+    print("[gpu-case] runtime switch against compiled-in alpha, 1080p", flush=True)
+    wl = W.billboards()
+    scene = rtx.upload_scene(wl.vertices, wl.geom_ids, wl.texcoords, wl.textures)
+    rays = torch.from_numpy(wl.rays).cuda()
+    n, sc = rays.shape[0], scene.view
+    out = torch.empty((n, 4), dtype=torch.float32, device="cuda")
+    params, ws, stream = rtx._params(scene, "alpha", 128, 8), rtx.Workspace("cuda"), torch.cuda.current_stream()
+    wptr, wb = ws.get(rtx.rt_trace_workspace_bytes(sc, n, 0))
+
+    def ms(flags):
+        return bench.timed(lambda: rtx.rt_trace_closest(
+            sc, rays.data_ptr(), n, rtx.KINDS["alpha"], params, flags, out.data_ptr(), None, wptr, wb,
+            stream.cuda_stream), 20, 3, stream)
+
+    both = [(ms(0), ms(rtx.RT_FLAG_RUNTIME_SWITCH)) for _ in range(5)]
+    compiled, switch = (min(x) for x in zip(*both))
+    assert switch < 1.1 * compiled, both
