@@ -82,8 +82,8 @@ class DifferentiableHit(torch.autograd.Function):
     def backward(ctx, grad_tuv, grad_prim=None, grad_hit=None):
         rays, hits, vertices, faces = ctx.saved_tensors
         n = rays.shape[0]
-        if grad_tuv is None:
-            grad_tuv = torch.zeros((n, 3), dtype=torch.float32, device=rays.device)
+        if grad_tuv is None:  # nothing depends on t, u and v
+            return (torch.zeros_like(rays), torch.zeros_like(vertices)) + (None,) * 11
         g = grad_tuv.contiguous().to(torch.float32)
         _same_cuda_device(rays=rays, hits=hits, vertices=vertices, faces=faces, grad_tuv=g)
         grad_vertices = torch.zeros_like(vertices)

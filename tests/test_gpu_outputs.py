@@ -44,3 +44,37 @@ def test_only_prim_used():
     assert prim.dtype == torch.int32 and hit.dtype == torch.bool and bool(hit[0]) and int(prim[0]) == 0
     gr, gv = torch.autograd.grad((tuv * 0).sum(), (r, v))
     assert torch.equal(gr, torch.zeros_like(r)) and torch.equal(gv, torch.zeros_like(v))
+
+
+def test_no_gradient_of_tuv(monkeypatch):
+    """An operation after the hit that has no gradient of its own: the rays and
+    vertices still get zeros, without a run of the adjoint."""
+    import numpy as np
+    import torch
+    from paper_1912_12786_amd import diff, rtx
+
+    class Stops(torch.autograd.Function):
+        @staticmethod
+        def forward(ctx, x):
+            return x.sum()
+
+        @staticmethod
+        def backward(ctx, g):
+            return None
+
+    def refuse(*a):
+        raise AssertionError("the adjoint ran")
+
+    monkeypatch.setattr(rtx, "rt_hit_backward", refuse)
+    print("[gpu-case] differentiable hit, no gradient of t, u, v", flush=True)
+    v = torch.tensor([[0., 0, 0], [1, 0, 0], [0, 1, 0]], device="cuda", requires_grad=True)
+    r = torch.tensor([[.2, .2, -1, 0, 0, 0, 1, np.inf]], dtype=torch.float32, device="cuda",
+                     requires_grad=True)
+    tuv, _, hit = diff.DifferentiableHit.apply(r, v, torch.tensor([[0, 1, 2]]), None, None, None)
+    assert bool(hit[0])
+    # and a path of its own for each input, so that the loss depends on both
+    gr, gv = torch.autograd.grad(Stops.apply(tuv) + (r[:, :3] + v[:1]).sum(), (r, v))
+    assert gr.tolist() == [[1, 1, 1, 0, 0, 0, 0, 0]] and gv.tolist() == [[1, 1, 1], [0, 0, 0], [0, 0, 0]]
+    gr, gv = torch.autograd.grad(Stops.apply(
+        diff.DifferentiableHit.apply(r, v, torch.tensor([[0, 1, 2]]), None, None, None)[0]), (r, v))
+    assert torch.equal(gr, torch.zeros_like(r)) and torch.equal(gv, torch.zeros_like(v))
