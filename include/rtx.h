@@ -105,8 +105,10 @@ typedef enum rt_isect_kind {
  * an 8 x 8 tile), in 64 steps of the box diagonal, and the chunks are handed
  * out in decreasing key order.  A ray's work grows with the length of scene it crosses, and the
  * launch ends when its last and longest rays do, so starting the long ones
- * first shortens the tail.  Only the schedule changes: every ray's result,
- * counters and output position are those of the call without it.  The
+ * first shortens the tail; a launch whose chunks all run at once (a wave each,
+ * 4 waves per SIMD or the fewer that RT_FLAG_WAVES_PER_SIMD asks for) is left
+ * as it is.  Only the schedule changes: every ray's result, counters and
+ * output position are those of the call without it.  The
  * workspace grows by 8 bytes per chunk plus 256 bytes per 256 chunks (or
  * part), rounded up to 16 (rt_trace_workspace_bytes with the same flags);
  * single-scene calls only (RT_ERR_UNSUPPORTED for batches). */
@@ -374,7 +376,11 @@ rt_status rt_bvh_refit(const rt_scene *scene, const uint32_t *plan, uint32_t n_t
 /* Device workspace a trace call needs (bytes, possibly 0): the ray queue
  * head of persistent launch shapes and overflow space for traversal stacks
  * deeper than the on-chip stack.  Its contents need no initialisation and
- * are scratch: calls that share a workspace must be ordered on one stream. */
+ * are scratch: calls that share a workspace must be ordered on one stream.
+ * A larger workspace makes small launches faster, with the same results: in
+ * shapes of 64 threads and chunks of 64 rays, fewer than 64 x 4096 rays are
+ * spread over up to 4,096 waves as far as workspace_bytes holds those waves'
+ * stacks.  The size for n_rays = 64 x 4096 (262,144) always does. */
 rt_status rt_trace_workspace_bytes(const rt_scene *scene, uint32_t n_rays, uint32_t flags,
                                    size_t *bytes);
 
@@ -457,7 +463,8 @@ rt_status rt_batch_table_bytes(uint32_t n_scenes, size_t *bytes);
 rt_status rt_batch_pack(const rt_batch_entry *entries, uint32_t n_scenes, rt_isect_kind kind,
                         void *host_table, size_t table_bytes, rt_batch_info *info);
 
-/* Workspace of rt_trace_batch (as rt_trace_workspace_bytes). */
+/* Workspace of rt_trace_batch (as rt_trace_workspace_bytes; a larger one helps
+ * small batches alike, the size for info->n_rays = 262,144 always). */
 rt_status rt_trace_batch_workspace_bytes(const rt_batch_info *info, uint32_t flags,
                                          size_t *bytes);
 

@@ -107,10 +107,16 @@ inline kernel_args scene_args(const rt_scene &scene, const void *rays, uint32_t 
 // for them.  The waves then begin with few rays, and lanes without one take
 // over parts of them.  Kernel times at 64 rays per wave and split: 1,024
 // triangles, 4,096 rays 35 -> 21 us; billboards under the alpha mask, 1,600 rays
-// 92 -> 55, 9,216 99 -> 59, 40,000 112 -> 75, 102,400 129 -> 109; four nearest
-// hits, which share no rays, 1,600 113 -> 59, 40,000 144 -> 145; scattered rays on
+// 92 -> 55, 9,216 99 -> 59, 40,000 112 -> 75, 102,400 129 -> 109; scattered rays on
 // spheres, 2,500 37 -> 30, 20,000 41 -> 39, 80,000 44 -> 44.  2,048 waves lose 5
 // to 15 % of that at 9,216 to 102,400 rays, 8,192 lose 10 % on scattered rays.
+// Queries that share no rays gain too, by fewer unlike rays in a wave (times of
+// the call): alpha mask with counters 1,600 rays 186 -> 113, 19,600 216 -> 182,
+// 40,000 222 -> 201; four nearest 1,600 270 -> 126, 9,216 345 -> 254, 40,000 375
+// -> 345; two scenes under the mask in a batch 9,216 180 -> 120, 40,000 247 ->
+// 212.  Between 60,000 and 130,000 rays they move by -12 to +16 %, most of them
+// faster: 102,400 in tiles lose (counters 232 -> 244, four nearest 388 -> 381,
+// without a mask 140 -> 156), 82,944 gain (237 -> 227, 390 -> 367, 147 -> 139).
 inline uint32_t split_chunk(const kernel_args &a, uint64_t max_waves)
 {
     uint32_t chunk = a.chunk;
