@@ -716,7 +716,7 @@ struct kernel_args {
     uint32_t tile_w8;    // tiled schedule: image width / 8 (0: rays in index order)
     uint32_t tiled;      // rays [0, tiled) are whole rows of 8 x 8 tiles
     const uint32_t *order;  // longest-path-first: chunk to take at each position (else null)
-    uint32_t chunk;      // rays per chunk: the launch shape's, or a smaller power of two >= 8
+    uint32_t chunk;      // rays per chunk: the launch shape's, or a smaller power of two down to 1
     uint64_t spill_threads;  // threads that the spill columns have room for (host only)
 };
 
@@ -1194,7 +1194,7 @@ struct shared_result<closest_result> {
     template <class Stack>
     __device__ __forceinline__ void settle(ray_state &r, Stack &st, uint32_t &cur, uint32_t &given)
     {
-        for (uint64_t hits = __ballot(r.tmax != told); hits != 0; hits &= hits - 1) {
+        for (uint64_t hits = __ballot(r.tmax < told); hits != 0; hits &= hits - 1) {
             const int l = __builtin_ctzll(hits);
             const uint32_t at = uint32_t(uintptr_t(entry));  // (LDS: the low word tells)
             const uint32_t e = __builtin_amdgcn_readlane(at, l);
