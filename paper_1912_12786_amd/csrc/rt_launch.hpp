@@ -12,7 +12,13 @@
 // and may be wrapped in counting_intersector<T> for the per-ray counters.
 // trace_custom<T>() then runs the closest-hit query with it, using the
 // library's default launch shape and the scene's node layout (rt_bvh_build,
-// rt_bvh_compress or rt_bvh_widen).
+// rt_bvh_compress or rt_bvh_widen).  accept() may keep state in the
+// intersector: one object serves one ray at a time, whose candidates it sees in
+// traversal order.  So the kernel does not share a wave's last rays, nor is a
+// small launch spread over more waves: an alpha mask written as user code takes
+// 522 us where the library's takes 447 (1080p, 64 rays to a wave in both), and
+// 156 against 56 for 64 x 64 rays; both took 624 and 193 before the traversal
+// stack was redone.
 #pragma once
 
 #include <hip/hip_runtime.h>

@@ -1,13 +1,16 @@
 """User intersectors from Python, compiled into their own traversal kernels.
 
 The paper's point (Section 3.2) is that the accept decision is a compile-time
-parameter of the traversal, so a user's filter costs what its own code costs
-and nothing more.  ``build_intersector`` generates a HIP source whose
-intersector has the given parameter fields and ``accept`` body, instantiates
-the library's traversal template with it (closest and any hit, with and
-without the counting wrapper, the library's default launch shape and the
-scene's node layout) and compiles it with librtx's flags into a shared library;
-``CustomIntersector`` traces with it.
+parameter of the traversal, so a user's filter is inlined where the built-in
+ones are.  (They alone share a wave's last rays among idle lanes, which takes
+a decision that keeps no state: written as user code the alpha mask takes 522
+us at 1080p where the built-in one takes 447, and 156 against 56 for 64 x 64
+rays.)  ``build_intersector`` generates a HIP source whose intersector has the
+given parameter fields and ``accept`` body, instantiates the library's
+traversal template with it (closest and any hit, with and without the counting
+wrapper, the library's default launch shape and the scene's node layout) and
+compiles it with librtx's flags into a shared library; ``CustomIntersector``
+traces with it.
 
 ``accept`` is the body of ``bool accept(const rtx::hit_candidate &c)``: it
 reads the candidate ``c`` (``c.prim_id`` -- the triangle's input index --
