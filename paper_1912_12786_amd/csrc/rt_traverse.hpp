@@ -1078,7 +1078,11 @@ constexpr bool is_stateless = std::is_same_v<Isect, default_intersector> ||
                               std::is_same_v<Isect, alpha_intersector> ||
                               std::is_same_v<Isect, checker_intersector>;
 
-// Accesses to what other lanes of the wave write and read.
+// Accesses to what other lanes of the wave write and read.  lds_step() between
+// two of them: every lane here makes the first before any makes the second (the
+// wave runs in step; without it the compiler may give lanes code of their own).
+__device__ __forceinline__ void lds_step() { __builtin_amdgcn_wave_barrier(); }
+
 template <class T>
 __device__ __forceinline__ T lds_load(const T *p)
 {
@@ -1186,6 +1190,7 @@ struct shared_result<closest_result> {
     {
         const uint64_t k = key(t, rank);
         lds_min(&entry->best, k);
+        lds_step();
         // of several lanes with hits of one ray, the one whose key is left
         if (lds_load(&entry->best) == k) {
             lds_store(&entry->t, t);
@@ -1237,7 +1242,9 @@ struct shared_result<closest_result> {
         }
         if (__builtin_amdgcn_uicmp(cur, kParked, kIcmpEQ) != 0 && cur != kNoRef) {
             lds_store(&entry->first, kNoRef);
+            lds_step();
             lds_min(&entry->first, rank);
+            lds_step();
             if (cur == kParked && lds_load(&entry->first) == rank) {
                 cur = leaf;
                 leaf = kNoRef;
@@ -1281,6 +1288,7 @@ struct shared_result<any_result> {
     __device__ __forceinline__ bool commit(ray_state &, float, float, float, uint32_t prim, uint32_t)
     {
         lds_min(&entry->best, rank);
+        lds_step();
         if (lds_load(&entry->best) == rank) lds_store(&entry->prim, prim);
         return true;
     }
