@@ -118,6 +118,47 @@ def test_closest_in_one_plane(env, oracle_lib, name, kind, n_rays):
             P.assert_exact_vs_b(P.hits_to_numpy(got[at]), B, what)
 
 
+def quads_on_a_grid(n, seed):
+    """n corners on a grid of 32 with a quad of one cell across each axis, many
+    of them twice: equal distances within a leaf and across leaves."""
+    c = np.round(np.random.default_rng(seed).uniform(0, 1, (n, 3)) * 32)
+    out = []
+    for a in range(3):
+        for t in (((0, 0), (1, 0), (1, 1)), ((0, 0), (1, 1), (0, 1))):
+            tri = np.repeat(c[:, None], 3, axis=1)
+            for k, (x, y) in enumerate(t):
+                tri[:, k, (a + 1) % 3] += x
+                tri[:, k, (a + 2) % 3] += y
+            out.append(tri)
+    return (np.stack(out, 1).reshape(-1, 3, 3) / 32).astype(np.float32)
+
+
+@pytest.mark.parametrize("max_leaf", [1, 2, 4, 7])
+@pytest.mark.parametrize("n_rays", [200_000, 20_000])
+def test_equal_distances_in_a_leaf(env, oracle_lib, max_leaf, n_rays):
+    """Rays from grid points along rational directions through quads on a grid,
+    hit after hit at one distance, also in the same leaf."""
+    torch, rtx = env
+    v = quads_on_a_grid(4000, 8)
+    bvh = oracle_lib.build_bvh(v, max_leaf=max_leaf)
+    edge = rays_of(n_rays)[n_rays:].copy()
+    edge[:, :2] = np.random.default_rng(3).integers(0, 65, (n_rays, 2)) / np.float32(64)
+    rays = torch.from_numpy(edge).cuda()
+    for layout in ("f32", "q8", "f32p", "wide4"):
+        sc = rtx.upload_scene(v, layout=layout, max_leaf=max_leaf)
+        B = oracle_lib.traverse(v, bvh, edge, "default", layout=layout)
+        for shape, kw in ways(torch, rtx, n_rays):
+            what = f"quads on a grid, leaves <= {max_leaf}, {layout} {n_rays} rays {shape} {sorted(kw)}"
+            announce(what)
+            try:
+                got = rtx.trace(sc, rays, shape=shape, **kw)
+            except rtx.RtxError as e:
+                assert e.status == rtx.RT_ERR_UNSUPPORTED
+                continue
+            torch.cuda.synchronize()
+            P.assert_exact_vs_b(P.hits_to_numpy(got), B, what)
+
+
 @pytest.mark.parametrize("kind", ["default", "procedural"])
 def test_batch_in_one_plane(env, oracle_lib, kind):
     torch, rtx = env
