@@ -648,9 +648,9 @@ struct multi_result {
 };
 
 // The triangles of one leaf, in stored order.  Returns true iff the result
-// policy finished the ray.  (A hit that has to wait ends the leaf, which is
-// tested again later: the hits before it are in the bound by then, while one
-// after it at the same distance must not come first.)
+// policy finished the ray.  (A leaf with a hit that has to wait is tested again
+// later: the hits before it are in the bound by then, and those after it wait
+// too, as one at the same distance must not come first.)
 template <class Result, class Isect>
 __device__ __forceinline__ bool leaf_step(const scene_view &sc, ray_state &r, Isect &isect,
                                           uint32_t ref, Result &res)
@@ -665,9 +665,7 @@ __device__ __forceinline__ bool leaf_step(const scene_view &sc, ray_state &r, Is
             bool ok = true;
             if constexpr (Isect::kFilters)
                 ok = isect.accept(hit_candidate{__float_as_uint(a.w), __float_as_uint(b.w), t, u, v});
-            if constexpr (Result::kWaits) {
-                if (ok && res.must_wait(r, ref, a, b, c, t)) return false;
-            }
+            if constexpr (Result::kWaits) ok = ok && !res.must_wait(r, ref, a, b, c, t);
             if (ok && res.commit(r, t, u, v, __float_as_uint(a.w), j)) return true;
         }
     }
@@ -1182,7 +1180,7 @@ struct shared_result<closest_result> {
                                               float4 c, float t)
     {
         const bool certain = uint32_t(root) == kNoRef ||
-                             (t >= entry_bound(a.x, b.x, c.x, r.ix, r.bx) &&
+                             (leaf == kNoRef && t >= entry_bound(a.x, b.x, c.x, r.ix, r.bx) &&
                               t >= entry_bound(a.y, b.y, c.y, r.iy, r.by) &&
                               t >= entry_bound(a.z, b.z, c.z, r.iz, r.bz));  // and t > tmin
         if (!certain) leaf = ref;
