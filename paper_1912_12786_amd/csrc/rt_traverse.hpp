@@ -451,11 +451,11 @@ __device__ __forceinline__ void node_children(const scene_view &sc, uint32_t cur
 
 // Order key of a four-wide child: hit children by (tn, child index), every
 // missed child after them.  The float's bit pattern is mapped to an unsigned
-// integer of the same order (negative values reversed), so one 64-bit
-// compare orders the pair.
+// integer of the same order (negative values reversed, both zeros as one, as
+// the float compare has them), so one 64-bit compare orders the pair.
 __device__ __forceinline__ uint64_t wide_key(bool hit, float tn, uint32_t c)
 {
-    const uint32_t b = __float_as_uint(tn);
+    const uint32_t b = __float_as_uint(tn + 0.0f);
     const uint32_t ord = (b & 0x80000000u) ? ~b : (b | 0x80000000u);
     return hit ? (uint64_t(ord) << 2 | c) : ~uint64_t(0);
 }

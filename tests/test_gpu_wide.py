@@ -274,3 +274,31 @@ def test_batch_wide(env, oracle_lib):
         sl = slice(batch.offsets[i], batch.offsets[i + 1])
         P.assert_exact_vs_b({k: v[sl] for k, v in g.items()}, B, f"batch wide4 {i}")
         P.assert_counters_vs_b(c_all[sl], B, f"batch wide4 scene {i}")
+
+
+@pytest.mark.parametrize("max_leaf", [1, 3])
+@pytest.mark.parametrize("seed", [0, 4, 19])
+def test_boxes_entered_at_zero(env, oracle_lib, seed, max_leaf):
+    """Rays that start before their origin and pass it on box faces: entries of
+    +0 and -0 are equal, and the lower child slot goes first."""
+    torch, rtx = env
+    g = np.random.default_rng(seed)
+    v = np.round(g.uniform(-1, 1, (1000, 1, 3)) * 4) / 4 + np.round(g.uniform(-1, 1, (1000, 3, 3))) / 4
+    axis, i = g.integers(0, 3, 1000), np.arange(1000)
+    v[i, :, axis] = v[i, :1, axis]
+    v = v.astype(np.float32)
+    r = np.zeros((20_000, 8), np.float32)
+    r[:, :3] = np.round(g.uniform(-1, 1, (20_000, 3)) * 4) / 4 * g.choice([-1, 1], (20_000, 3))
+    r[:, 3] = g.uniform(-0.5, 0.5, 20_000)
+    r[:, 4:7] = np.round(g.uniform(-1, 1, (20_000, 3)) * 8) / 8
+    r[(r[:, 4:7] == 0).all(1), 6] = 1
+    r[:, 7] = np.inf
+    announce(f"wide nodes entered at zero, seed {seed}, leaves <= {max_leaf}")
+    sc = rtx.upload_scene(v, layout="wide4", max_leaf=max_leaf)
+    B = oracle_lib.traverse(v, oracle_lib.build_bvh(v, max_leaf=max_leaf), r, "default", layout="wide4")
+    rays = torch.from_numpy(r).cuda()
+    for count in (True, False):
+        got = rtx.trace(sc, rays, count=count)
+        torch.cuda.synchronize()
+        P.assert_exact_vs_b(P.hits_to_numpy(got[0] if count else got), B, f"seed {seed} count={count}")
+    P.assert_counters_vs_b(rtx.trace(sc, rays, count=True)[1], B, f"seed {seed}")
